@@ -887,7 +887,10 @@ size_t DevProblem::plan(const Symbolic &sy, int precision, int max_iters, Offset
   o.part_pq = L.take(npcg * 8);
   o.part_cg[0] = L.take(3 * npcg * 8);
   o.part_cg[1] = L.take(3 * npcg * 8);
-  o.cg_flag = L.take(npcg * 4);
+  for (int b = 0; b < 2; ++b) {  // 64-bit words of 32 bits each
+    o.cg_xw[b] = L.take(Cf * 6 * (T / 4) * 8);
+    o.cg_xp[b] = L.take(npcg * 6 * 8);
+  }
   o.part_rr = L.take(npcg * 8);
   o.part_cull = L.take(npt * 8);
   o.iter_cost = rep + RL.ic;
@@ -1052,7 +1055,10 @@ int DevProblem::init(const Symbolic &sy, const ba_problem_desc *d, const ba_opti
   pd.part_pq = (double *)ptr(off.part_pq);
   pd.part_cg[0] = (double *)ptr(off.part_cg[0]);
   pd.part_cg[1] = (double *)ptr(off.part_cg[1]);
-  pd.cg_flag = (uint32_t *)ptr(off.cg_flag);
+  for (int b = 0; b < 2; ++b) {
+    pd.cg_xw[b] = (uint64_t *)ptr(off.cg_xw[b]);
+    pd.cg_xp[b] = (uint64_t *)ptr(off.cg_xp[b]);
+  }
   pd.part_rr = (double *)ptr(off.part_rr);
   pd.part_cull = (int32_t *)ptr(off.part_cull);
   pd.st = (LMState *)ptr(off.st);

@@ -222,7 +222,8 @@ struct ProbDev {
   double *part_rz[2];             // [n_pcg_tiles]
   double *part_pq;                // [n_pcg_tiles]
   double *part_cg[2];             // [3][n_pcg_tiles] r.u, w.u, r.r partials by parity
-  uint32_t *cg_flag;              // [n_pcg_tiles] resident PCG: iterations each tile has finished
+  uint64_t *cg_xw[2];             // [6 Cf][words of T] resident PCG: stamped w by parity (see k_cg_run)
+  uint64_t *cg_xp[2];             // [6][n_pcg_tiles] ... stamped words of the r.u, w.u, r.r partials
   double *part_rr;                // [n_pcg_tiles]
   int32_t *part_cull;             // [n_pt_tiles][2] active observations, points with one, after culling
   LMState *st;

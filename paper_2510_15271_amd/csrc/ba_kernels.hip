@@ -284,6 +284,24 @@ __device__ inline T wave_sum(T v) {
   return lane_pair_sum<1>(v);
 }
 
+// v of lane (a / 4 + K): a is a lane's byte address, K a constant folded into the
+// instruction's offset (lane indices kept per K would each hold a register).
+template <int K, class T>
+__device__ __forceinline__ T lane_read(int a, T v) {
+  int w[sizeof(T) / 4];
+  __builtin_memcpy(w, &v, sizeof(T));
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(T) / 4); ++i) w[i] = __builtin_amdgcn_ds_bpermute(a + 4 * K, w[i]);
+  __builtin_memcpy(&v, w, sizeof(T));
+  return v;
+}
+// v of lanes a / 4, a / 4 + D, ... (N of them), added in that order from 0
+template <int N, int D, class T>
+__device__ __forceinline__ T lane_stride_sum(int a, T v) {
+  if constexpr (N == 0) return T(0);
+  else return lane_stride_sum<N - 1, D>(a, v) + lane_read<(N - 1) * D>(a, v);
+}
+
 // Adds one pass of kObsChunk observations' NV values (c; jl = their point in the
 // tile, -1 for none) into the points' accumulators s_acc.  The observations of one
 // point are consecutive, so an inclusive
@@ -1901,6 +1919,10 @@ __device__ inline void cg_partials(double *part, int n_tiles, int tile, double g
   }
 }
 
+// 64-bit exchange words per value of the resident PCG (k_cg_run)
+template <class T>
+constexpr int cg_words() { return (int)sizeof(T) / 4; }
+
 // NW waves per tile, wave w taking rows w, w + NW, ...: 4 for 4-row tiles (and mixed
 // batches), 16 for tiles of 16 or 32 rows, so that no wave walks more than two rows.
 template <class T, int NW>
@@ -1911,7 +1933,14 @@ __global__ __launch_bounds__(64 * NW) void k_cg_start(const ProbDev *__restrict_
   LMState *st = pd.st;
   __shared__ int s_flag[1];
   __shared__ double s_red[3 * NW];
-  if (threadIdx.x == 0) pd.cg_flag[tl.idx] = 0u;  // the resident PCG's barrier flags
+  // the resident PCG's exchange words: this tile's rows and partials, both parities
+  {
+    const size_t e0 = 6 * (size_t)cg_words<T>() * tl.idx * pd.pcg_rows;
+    const int ne = 6 * cg_words<T>() * (min(pd.Cf, (tl.idx + 1) * pd.pcg_rows) - tl.idx * pd.pcg_rows);
+    for (int k = threadIdx.x; k < ne; k += 64 * NW)
+      for (int b = 0; b < 2; ++b) pd.cg_xw[b][e0 + k] = 0u;
+    if (threadIdx.x < 12) pd.cg_xp[threadIdx.x / 6][(size_t)(threadIdx.x % 6) * pd.n_pcg_tiles + tl.idx] = 0u;
+  }
   if (threadIdx.x == 0) s_flag[0] = lm_active(st) ? 1 : 0;
   __syncthreads();
   if (!s_flag[0]) return;
@@ -2333,197 +2362,255 @@ __global__ __launch_bounds__(1024) void k_cg_step1(const ProbDev pd, int it) {
 // launch (partial sums; w, s and r of a tile's own rows): agent-coherent accesses,
 // served at the device's coherence point rather than from an XCD's L2, since the L2s
 // of the eight XCDs are not coherent with each other.
-template <class V>
-__device__ inline V ld_shared(const V *p) {
-  return __hip_atomic_load(const_cast<V *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ uint64_t ld_shared(global_t<uint64_t> *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-template <class V>
-__device__ inline void st_shared(V *p, V v) {
+__device__ __forceinline__ void st_shared(global_t<uint64_t> *p, uint64_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Grid barrier of the resident PCG.  Each wave waits until its stores have been
-// acknowledged (the shared values above are written agent-coherent, so acknowledged
-// means visible to every XCD); thread 0 then sets the tile's flag, and wave 0 polls
-// every tile's flag (one agent-coherent load per lane and 64 tiles) until all have
-// reached `stamp`.  Readers take the shared values with agent-coherent loads issued
-// after the poll, so neither an L2 write-back nor an invalidate is needed: the form
-// with a release/acquire pair per workgroup measured 9.3 us per iteration with one
-// counter and 8.3 us with per-tile flags, this form 7.2 us, and a launch per iteration
-// 8.0 us (2M-observation drive).
-// The wait is bounded: after `polls` polls (LMState::bar_polls) the workgroup reports
-// failure, so a launch whose workgroups cannot all be resident at once ends instead of
-// waiting forever.
-__device__ inline bool grid_barrier(uint32_t *flag, int n_tiles, int tile, uint32_t stamp, int polls,
-                                    int *s_ok) {
-  __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  const int t = threadIdx.x;
-  if (t < 64) {
-    if (t == 0) st_shared(flag + tile, stamp);
-    bool all = false;
-    for (int n = 0; n < polls; ++n) {
-      // a lane's flags (up to four: 256 tiles) are loaded together, so that one poll
-      // costs one round trip; a loop over them waited for each load before the next
-      // (lanes past the last tile load its flag again: every load is unconditional)
-      bool mine = true;
-      uint32_t v[4];
+// What the tiles of the resident PCG hand each other is one value per row element (w) and
+// three partial sums per tile and iteration.  Each travels as 64-bit words that carry 32 bits
+// of the value and, above them, the iteration it belongs to (its stamp): a reader polls the
+// word itself until the stamp is the one it waits for.  No flag and no store
+// acknowledgement stands between the store and the load that sees it, so an iteration
+// costs one trip through the coherence point; the form with a grid barrier (store, wait for
+// the acknowledgement, set the tile's flag, poll all flags, load the values) took three.
+// Two buffers by parity suffice: a tile stores iteration k + 1 only after it has read every
+// tile's partials of iteration k, and a tile stores those after its own reads of k - 1.
+// k_cg_start clears the words (stamps count from 1).
+template <class T>
+__device__ __forceinline__ void st_stamped(global_t<uint64_t> *p, T v, uint32_t stamp) {
+  uint32_t w[cg_words<T>()];
+  __builtin_memcpy(w, &v, sizeof(T));
 #pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = ld_shared(flag + min(t + 64 * q, n_tiles - 1));
-#pragma unroll
-      for (int q = 0; q < 4; ++q) mine = mine & (v[q] >= stamp);
-      for (int k = t + 256; k < n_tiles; k += 64) mine = mine & (ld_shared(flag + k) >= stamp);
-      all = __all(mine) != 0;
-      if (all) break;
-      __builtin_amdgcn_s_sleep(1);
-    }
-    if (t == 0) s_ok[0] = all ? 1 : 0;
+  for (int i = 0; i < cg_words<T>(); ++i) st_shared(p + i, ((uint64_t)stamp << 32) | w[i]);
+}
+// A tile's three partial sums, word j of tile k at j * nt + k (a reader's 64 lanes then load
+// one contiguous run per word; with a tile's six words together each of its loads touched
+// 24 lines, and the polls of 125 tiles queued on them), one lane per word.
+__device__ __forceinline__ void st_partials(global_t<uint64_t> *xp, int nt, int tile, double g, double d, double r,
+                                            uint32_t stamp) {
+  const int j = (int)threadIdx.x & 63;
+  if (j < 6) {
+    const double v = j < 2 ? g : j < 4 ? d : r;
+    uint64_t b;
+    __builtin_memcpy(&b, &v, 8);
+    st_shared(xp + ((uint32_t)(j * nt) + (uint32_t)tile), ((uint64_t)stamp << 32) | (uint32_t)(b >> (32 * (j & 1))));
   }
-  __syncthreads();
-  return s_ok[0] != 0;
+}
+template <class T>
+__device__ __forceinline__ T stamped_value(const uint64_t *v) {
+  uint32_t w[cg_words<T>()];
+#pragma unroll
+  for (int i = 0; i < cg_words<T>(); ++i) w[i] = (uint32_t)v[i];
+  T o;
+  __builtin_memcpy(&o, w, sizeof(T));
+  return o;
 }
 
 // The whole one-reduction PCG of one problem in one launch, for a grid whose tiles are
 // all resident at once (checked by the host): the same iterates in the same order as
-// pcg_max launches of k_cg_step1, with a grid barrier where a launch boundary was.
+// pcg_max launches of k_cg_step1, with the exchange above where a launch boundary was.
 // What a launch re-read every iteration stays on chip for the whole solve: the tile's
 // S blocks in registers (those a lane group holds; longer rows read the rest each
-// iteration), the M^-1 rows of its columns in LDS, and u, p and x of its own rows in
-// registers.  Per iteration a tile reads only the partial sums and w, s and r of its
-// columns, and stores w, s and r of its own rows (x once at the end).  pd.cg_flag
-// holds the barrier's per-tile flags, cleared by k_cg_start.
+// iteration), the M^-1 rows of its columns, u, p and x of its own rows, and s and r of
+// every column it reads: each tile advances them from w by itself, with the same
+// operations as the column's owner, so that w alone is exchanged.  Columns lie ten to a
+// wave (six lanes each), so that a column's r is handed to its lanes by shuffles.  A tile
+// with more than 160 columns takes a second set of ten per wave (NS = 2).
+// Against the grid-barrier form, which exchanged w, s and r, read by all six lanes of a
+// column, an iteration of the 500-camera drive (2.3M observations) went from 8.4 to
+// 3.7 us.
+constexpr int kCgRunTiles = 320;                                  // tiles at most
+constexpr int kCgRunFew = 16;                                      // up to which polls do not get in each other's way
+constexpr int kCgWaveCols = 10;                                   // columns per wave and set
+constexpr int kCgSetCols = kCgWaveCols * (kCgThreads / 64);      // 160
+// S blocks per lane group held for the whole solve: what fits 128 VGPRs (16 waves per CU)
+// without spills, since a spilled register's reload waits for every store in flight
+template <class T, int R, int NS>
+constexpr int cg_run_pre() {
+  if (sizeof(T) == 8) return NS == 1 && R != kPcgRowsSparse ? 2 : 1;
+  return R == kPcgRows ? 4 : R == kPcgRowsMax ? (NS == 1 ? 4 : 3) : (NS == 1 ? 6 : 4);
+}
 
-// Dynamic LDS of k_cg_run: u of the tile's columns, then their M^-1 rows (FP64).
+// Dynamic LDS of k_cg_run: u of the tile's columns, then each thread's M^-1 rows (FP64).
 __host__ __device__ constexpr size_t cg_run_mrow_offset(int max_tcols, size_t tbytes) {
   return (6 * (size_t)max_tcols * tbytes + 7) / 8;  // in doubles
 }
 size_t cg_run_lds_bytes(int max_tcols, size_t tbytes) {
-  return 8 * cg_run_mrow_offset(max_tcols, tbytes) + 36 * sizeof(double) * (size_t)max_tcols;
+  return 8 * cg_run_mrow_offset(max_tcols, tbytes) +
+         6 * sizeof(double) * kCgThreads * (max_tcols > kCgSetCols ? 2 : 1);
 }
 
-template <class T, int RC>
+template <class T, int R, int NS>
 __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
   extern __shared__ double s_dyn[];
   T *ul = (T *)s_dyn;  // [tile columns][6]: u_{it+1} of every column this tile reads
-  // [tile columns][6][6]: M^-1 rows (in LDS: the S blocks fill the registers)
+  // [set][thread][6] M^-1 rows (in LDS: the S blocks fill the registers)
   double *ml = s_dyn + cg_run_mrow_offset(pd.max_tcols, sizeof(T));
-  __shared__ double s_red[48];
-  __shared__ T s_w[kPcgRowsMax][4][6];
-  __shared__ T s_ro[kPcgRowsMax][6], s_uo[kPcgRowsMax][6];
+  constexpr int kPw = (kCgRunTiles + 63) / 64;  // waves that sum the tiles' partials
+  __shared__ double s_pd[3][kCgRunTiles];       // r.u, w.u, r.r partials of every tile
+  __shared__ double s_red[3 * kPw];
+  __shared__ T s_w[R][4][6];
+  __shared__ T s_ro[6 * R], s_uo[6 * R], s_po[6 * R], s_xo[6 * R];  // r, u, p, x of the own rows
   __shared__ int s_flag[2];
   const int tile = blockIdx.x;
   LMState *st = pd.st;
-  const int t = threadIdx.x;
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int nt = pd.n_pcg_tiles;
-  const int R = RC ? RC : pd.pcg_rows;
-  const int Lr = kCgThreads / R;
-  const int wpr = Lr >= 64 ? Lr / 64 : 1;
+  constexpr int Lr = kCgThreads / R;            // lanes per row
+  constexpr int wpr = Lr >= 64 ? Lr / 64 : 1;  // waves per row
+  constexpr uint32_t W = cg_words<T>();
   const int row0 = tile * R, row1 = min(pd.Cf, row0 + R);
-  const int ncmax = pd.max_tcols;  // at most kCgColThreads / 6: one sweep holds every column
-  const int32_t *tcol = pd.tcol + (size_t)tile * ncmax;
-  const T *S = (const T *)pd.S;
-  T *x = (T *)pd.x;
-  if (t == 0) s_flag[0] = (lm_active(st) && !st->pcg_done) ? 1 : 0;
+  const int ncmax = pd.max_tcols;
+  const auto S = as_global((const T *)pd.S);
+  const auto S_lcol = as_global(pd.S_lcol);
+  const auto x = as_global((T *)pd.x);
+  if (t == 0) {
+    s_flag[0] = (lm_active(st) && !st->pcg_done) ? 1 : 0;
+    s_flag[1] = 0;
+  }
+  if (t < 3 * kPw) s_red[t] = 0.0;
   __syncthreads();
   if (!s_flag[0]) return;
   n_iter = min(n_iter, st->pcg_max);
   const double tol = st->pcg_tol, bb = st->pcg_bb;
   const int polls = st->bar_polls;
-  // ---- per-solve constants and the own-row state
-  const int l = t / 6, m = t - 6 * (t / 6);
-  const int c = (t < kCgColThreads && l < ncmax) ? tcol[l] : -1;
-  const bool has_col = c >= 0;
-  const bool own = has_col && c >= row0 && c < row1;
-  T um = T(0), pm = T(0), xm = T(0);  // u_it, p_{it-1} (p_{-1} = 0), x_it of an own element
-  if (has_col) {  // each thread reads back only the row it wrote
+  // ---- per-solve constants and the state of the tile's columns and own rows
+  const bool col_lane = lane < 6 * kCgWaveCols;
+  const int cg = col_lane ? lane / 6 : kCgWaveCols - 1, m = col_lane ? lane - 6 * cg : 0;
+  int own[NS], ulo[NS];      // position among the own rows' elements and in ul, -1: none
+  uint32_t ce[NS];           // element of the column (lanes without one: of an own row)
+  T wc[NS], sc[NS], rc[NS];  // w, s and r of the column's element
 #pragma unroll
-    for (int n = 0; n < 6; ++n) ml[6 * t + n] = pd.Minv[36 * (size_t)c + 6 * m + n];
+  for (int k = 0; k < NS; ++k) {
+    const int lc = kCgSetCols * k + kCgWaveCols * wv + cg;
+    const int cc = col_lane && lc < ncmax ? as_global(pd.tcol)[(size_t)tile * ncmax + lc] : -1;
+    ulo[k] = cc >= 0 ? 6 * lc + m : -1;
+    own[k] = cc >= row0 && cc < row1 ? 6 * (cc - row0) + m : -1;
+    const int c = cc >= 0 ? cc : row0;
+    ce[k] = 6 * (uint32_t)c + (uint32_t)m;
+    wc[k] = as_global((const T *)pd.cg_w[0])[ce[k]];
+    rc[k] = as_global((const T *)pd.cg_r[0])[ce[k]];
+    sc[k] = T(0);  // s_{-1}
+    if (own[k] >= 0) {
+      s_uo[own[k]] = as_global((const T *)pd.cg_u[0])[ce[k]];
+      s_xo[own[k]] = x[ce[k]];
+      s_po[own[k]] = T(0);  // p_{-1}
+    }
+#pragma unroll
+    for (int n = 0; n < 6; ++n)  // each thread reads back only the row it wrote
+      ml[6 * (kCgThreads * k + t) + n] = as_global((const double *)pd.Minv)[36 * (size_t)c + 6 * m + n];
   }
-  if (own) {
-    um = ((const T *)pd.cg_u[0])[6 * (size_t)c + m];
-    xm = x[6 * (size_t)c + m];
-  }
-  const int lrs = R == kPcgRows ? 8 : (R == kPcgRowsSparse ? 6 : 5);  // log2(Lr)
-  const int lane = t & 63, rw = t >> lrs;
-  const int h = t & (Lr - 1);
+  const int rw = t / Lr, h = t % Lr;
   const int q = Lr >= 64 ? (h >> 6) : 0;
   const int hs = Lr >= 64 ? (h & 63) : h;
-  const int gps = Lr >= 64 ? 10 : 5;
+  constexpr int gps = Lr >= 64 ? 10 : 5;
   const int g = hs / 6, i = hs - 6 * (hs / 6);
   const int a = row0 + rw;
-  const int bstep = gps * wpr;
-  const bool spl = g < gps && a < row1;
+  constexpr int bstep = gps * wpr;
   int b0 = 0, b1 = 0;
-  if (spl) {
-    b0 = pd.S_rowptr[a] + gps * q + g;
-    b1 = pd.S_rowptr[a + 1];
+  if (g < gps && a < row1) {
+    b0 = as_global(pd.S_rowptr)[a] + gps * q + g;
+    b1 = as_global(pd.S_rowptr)[a + 1];
   }
-  constexpr int kCgPre = sizeof(T) == 4 ? 3 : 1;  // S blocks per lane group held for the solve
-  T sreg[kCgPre][6];
-  int lreg[kCgPre];
+  constexpr int kPre = cg_run_pre<T, R, NS>();
+  T sreg[kPre][6];
+  int lreg[kPre];  // the block's column in ul (a block the lane does not have: 0 times column 0)
 #pragma unroll
-  for (int k = 0; k < kCgPre; ++k) {
+  for (int k = 0; k < kPre; ++k) {
     const int blk = b0 + bstep * k;
-    lreg[k] = -1;
-    if (blk < b1) {
-      lreg[k] = pd.S_lcol[blk];
+    const bool has = blk < b1;
+    lreg[k] = has ? 6 * S_lcol[blk] : -1;
 #pragma unroll
-      for (int n = 0; n < 6; ++n) sreg[k][n] = S[36 * (size_t)blk + 6 * i + n];
-    } else {
-#pragma unroll
-      for (int n = 0; n < 6; ++n) sreg[k][n] = T(0);
-    }
+    for (int n = 0; n < 6; ++n) sreg[k][n] = has ? S[36 * (size_t)blk + 6 * i + n] : T(0);
   }
-  const bool first = tile == 0 && t == 0;
+  // this thread's share of the tiles' partial words (word j of tile k at j * nt + k) and
+  // where they go in s_pd; then the waves that sum them (thread k: tile k, as in the
+  // per-launch step)
+  uint32_t pe[2], pl[2];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) {
+    pe[b] = min((uint32_t)(t + kCgThreads * b), 6 * (uint32_t)nt - 1);
+    const uint32_t j = pe[b] / (uint32_t)nt;
+    pl[b] = 2 * ((j >> 1) * kCgRunTiles + (pe[b] - j * (uint32_t)nt)) + (j & 1);
+  }
+  const bool two_words = 6 * nt > kCgThreads, sums = 64 * wv < nt;
+  for (int k = t; k < 3 * nt; k += kCgThreads) s_pd[k / nt][k % nt] = as_global((const double *)pd.part_cg[0])[k];
+  const auto xw0 = as_global(pd.cg_xw[0]), xw1 = as_global(pd.cg_xw[1]);
+  const auto xp0 = as_global(pd.cg_xp[0]), xp1 = as_global(pd.cg_xp[1]);
   double gprev = 1.0, aprev = 1.0;  // gamma_{it-1}, alpha_{it-1}
   bool ok = true;
+  int done_it = -1;
   for (int it = 0; it < n_iter; ++it) {
-    const int pr = it & 1, cu = pr ^ 1;
-    // ---- partials of iteration it and the vectors of this tile's columns
-    double pg = 0.0, pdl = 0.0, prr = 0.0;
-    {
-      const double *part = pd.part_cg[pr];
-      for (int k = t; k < nt; k += kCgThreads) {
-        pg += ld_shared(part + k);
-        pdl += ld_shared(part + nt + k);
-        prr += ld_shared(part + 2 * nt + k);
-      }
-    }
-    T cw[6], cs[6], cr[6];
-    if (has_col) {
-      const T *w0 = (const T *)pd.cg_w[pr];
-      const T *s0 = (const T *)pd.cg_s[pr];
-      const T *r0 = (const T *)pd.cg_r[pr];
-      const size_t b = 6 * (size_t)c;
+    if (it > 0) {
+      // ---- w_it of this tile's columns and the partials of iteration it
+      const auto xw = (it & 1) ? xw1 : xw0, xp = (it & 1) ? xp1 : xp0;
+      const uint32_t stamp = (uint32_t)it;
+      // the first poll waits about as long as the values take: polls that come too early
+      // queue up in front of the stores they wait for (125 tiles: 6.3 us per iteration
+      // without the pause, 4.5 at 15 units of 64 clocks, 3.7 at 25, 4.0 at 40; 2 tiles: 5.1,
+      // 4.4 at 10, 4.6 at 25)
+      if (nt > kCgRunFew) __builtin_amdgcn_s_sleep(25);
+      else __builtin_amdgcn_s_sleep(10);
+      bool all = false;
+      uint64_t xv[NS][W], pv[2];
+      for (int n = 0; n < polls && !all; ++n) {
 #pragma unroll
-      for (int n = 0; n < 6; ++n) {
-        cw[n] = ld_shared(w0 + b + n);
-        cs[n] = ld_shared(s0 + b + n);
-        cr[n] = ld_shared(r0 + b + n);
+        for (int k = 0; k < NS; ++k)
+#pragma unroll
+          for (uint32_t j = 0; j < W; ++j) xv[k][j] = ld_shared(xw + (W * ce[k] + j));
+        pv[0] = ld_shared(xp + pe[0]);
+        if (two_words) pv[1] = ld_shared(xp + pe[1]);
+        bool mine = (uint32_t)(pv[0] >> 32) == stamp;
+        if (two_words) mine = mine & ((uint32_t)(pv[1] >> 32) == stamp);
+#pragma unroll
+        for (int k = 0; k < NS; ++k)
+#pragma unroll
+          for (uint32_t j = 0; j < W; ++j) mine = mine & ((uint32_t)(xv[k][j] >> 32) == stamp);
+        all = __all(mine) != 0;
       }
-    }
-    pg = wave_sum(pg);
-    pdl = wave_sum(pdl);
-    prr = wave_sum(prr);
-    if (lane == 0) {
-      s_red[t >> 6] = pg;
-      s_red[16 + (t >> 6)] = pdl;
-      s_red[32 + (t >> 6)] = prr;
+      if (all) {
+#pragma unroll
+        for (int k = 0; k < NS; ++k) wc[k] = stamped_value<T>(xv[k]);
+        ((uint32_t *)&s_pd[0][0])[pl[0]] = (uint32_t)pv[0];
+        if (two_words) ((uint32_t *)&s_pd[0][0])[pl[1]] = (uint32_t)pv[1];
+      }
+      if (!all && lane == 0) s_flag[1] = 1;
     }
     __syncthreads();
-    double gam = 0.0, del = 0.0, rr = 0.0;
+    if (sums) {
+      double v0 = 0.0, v1 = 0.0, v2 = 0.0;
+      if (t < nt) {
+        v0 = s_pd[0][t];
+        v1 = s_pd[1][t];
+        v2 = s_pd[2][t];
+      }
+      v0 = wave_sum(v0);
+      v1 = wave_sum(v1);
+      v2 = wave_sum(v2);
+      if (lane == 0) {
+        s_red[wv] = v0;
+        s_red[kPw + wv] = v1;
+        s_red[2 * kPw + wv] = v2;
+      }
+    }
+    __syncthreads();
+    if (s_flag[1]) {
+      ok = false;
+      break;
+    }
+    double gam = s_red[0], del = s_red[kPw], rr = s_red[2 * kPw];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
+    for (int k = 1; k < kPw; ++k) {
       gam += s_red[k];
-      del += s_red[16 + k];
-      rr += s_red[32 + k];
+      del += s_red[kPw + k];
+      rr += s_red[2 * kPw + k];
     }
     // every tile takes the same decisions from the same sums
     if (it > 0 && sqrt(rr) <= tol * sqrt(bb)) {
-      if (first) {
-        st->pcg_done = 1;
-        st->pcg_iters = it;
-      }
+      done_it = it;
       break;
     }
     double beta = 0.0, den = del;
@@ -2532,120 +2619,103 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
       den = del - beta * gam / aprev;
     }
     if (!(den > 0.0)) {
-      if (first) {
-        st->pcg_done = 1;
-        st->pcg_iters = it + 1;
-      }
+      done_it = it + 1;
       break;
     }
     const double alpha = gam / den;
-    if (first) {
-      st->cg_alpha[cu] = alpha;
-      st->cg_gamma[cu] = gam;
-    }
     gprev = gam;
     aprev = alpha;
     const T ta = T(alpha), tb = T(beta);
-    // ---- columns: s_it, r_{it+1}, u_{it+1}; own rows p_it and x_{it+1}
-    T sm = T(0), rm = T(0), un = T(0), pn = T(0);
-    if (has_col) {
-      double mrow[6];
+    // ---- columns: s_it, r_{it+1}, u_{it+1} = M^-1 r_{it+1}; own rows p_it and x_{it+1}
 #pragma unroll
-      for (int n = 0; n < 6; ++n) mrow[n] = ml[6 * t + n];
-      cg_column<T>(m, tb, ta, cw, cs, cr, mrow, sm, rm, un);
-      ul[6 * l + m] = un;
-      if (own) {
-        pn = um + tb * pm;
-        s_ro[c - row0][m] = rm;
-        s_uo[c - row0][m] = un;
+    for (int k = 0; k < NS; ++k) {
+      sc[k] = wc[k] + tb * sc[k];
+      rc[k] = rc[k] - ta * sc[k];
+      const int ca = 4 * (lane - m);  // the column's first lane
+      const T rn[6] = {lane_read<0>(ca, rc[k]), lane_read<1>(ca, rc[k]), lane_read<2>(ca, rc[k]),
+                       lane_read<3>(ca, rc[k]), lane_read<4>(ca, rc[k]), lane_read<5>(ca, rc[k])};
+      double z = 0.0;
+#pragma unroll
+      for (int n = 0; n < 6; ++n) z += ml[6 * (kCgThreads * k + t) + n] * (double)rn[n];
+      const T un = T(z);
+      if (ulo[k] >= 0) ul[ulo[k]] = un;
+      if (own[k] >= 0) {
+        const T pn = s_uo[own[k]] + tb * s_po[own[k]];
+        s_po[own[k]] = pn;
+        s_xo[own[k]] = s_xo[own[k]] + ta * pn;
+        s_uo[own[k]] = un;
+        s_ro[own[k]] = rc[k];
       }
     }
+    if (it + 1 == n_iter) break;  // the last x is formed: no tile reads a further product
     __syncthreads();
     // ---- w_{it+1} = S u_{it+1} for the tile's rows
     T acc = T(0);
-    if (spl) {
 #pragma unroll
-      for (int k = 0; k < kCgPre; ++k)
-        if (lreg[k] >= 0) {
-          const T *uc = ul + 6 * lreg[k];
+    for (int k = 0; k < kPre; ++k)
+      if (lreg[k] >= 0) {
+        const T *uc = ul + lreg[k];
 #pragma unroll
-          for (int n = 0; n < 6; ++n) acc += sreg[k][n] * uc[n];
-        }
-      for (int blk = b0 + bstep * kCgPre; blk < b1; blk += bstep) {
-        const T *Srow = S + 36 * (size_t)blk + 6 * i;
-        const T *uc = ul + 6 * pd.S_lcol[blk];
-#pragma unroll
-        for (int n = 0; n < 6; ++n) acc += Srow[n] * uc[n];
+        for (int n = 0; n < 6; ++n) acc += sreg[k][n] * uc[n];
       }
-    }
-    T wi = T(0);
-    if (Lr >= 64) {
+    for (int blk = b0 + bstep * kPre; blk < b1; blk += bstep) {
+      const auto Srow = S + 36 * (size_t)blk + 6 * i;
+      const T *uc = ul + 6 * S_lcol[blk];
 #pragma unroll
-      for (int gg = 0; gg < 10; ++gg) wi += __shfl(acc, 6 * gg + i, 64);
-    } else {
-      const int sbase = t & 32;
-#pragma unroll
-      for (int gg = 0; gg < 5; ++gg) wi += __shfl(acc, sbase + 6 * gg + i, 64);
+      for (int n = 0; n < 6; ++n) acc += Srow[n] * uc[n];
     }
+    // the group sums in group order, in the lanes of the row's first group
+    const T wi = lane_stride_sum<gps, 6>(Lr >= 64 ? 4 * i : 4 * ((t & 32) + i), acc);
     if (hs < 6 && a < row1) s_w[rw][q][hs] = wi;
     __syncthreads();
-    if (own) {
-      const size_t idx = 6 * (size_t)c + m;
-      st_shared((T *)pd.cg_s[cu] + idx, sm);
-      st_shared((T *)pd.cg_r[cu] + idx, rm);
-      pm = pn;
-      xm = xm + ta * pn;
-      um = un;
-    }
     // ---- w_{it+1} of the tile's rows and its partials of gamma_{it+1}, delta_{it+1},
     // ||r_{it+1}||^2 (as the per-launch step: wave 0 alone when 6 R <= 64)
-    const bool one_wave = 6 * R <= 64;
-    if (one_wave ? t < 64 : t < 256) {
+    constexpr bool one_wave = 6 * R <= 64;
+    const auto xw = (it & 1) ? xw0 : xw1;
+    const auto xp = (it & 1) ? xp0 : xp1;
+    const uint32_t stamp = (uint32_t)it + 1;
+    if (one_wave ? wv == 0 : wv < 4) {
       double g2 = 0.0, d2 = 0.0, q2 = 0.0;
-      if (t < 6 * R) {
+      if (t < 6 * (row1 - row0)) {
         const int rr_ = t / 6, mm = t - 6 * (t / 6);
-        const int a2 = row0 + rr_;
-        if (a2 < row1) {
-          T w = s_w[rr_][0][mm];
-          for (int qq = 1; qq < wpr; ++qq) w += s_w[rr_][qq][mm];
-          st_shared((T *)pd.cg_w[cu] + 6 * (size_t)a2 + mm, w);
-          const double ui = (double)s_uo[rr_][mm], ri = (double)s_ro[rr_][mm];
-          g2 = ri * ui;
-          d2 = (double)w * ui;
-          q2 = ri * ri;
-        }
+        T w = s_w[rr_][0][mm];
+#pragma unroll
+        for (int qq = 1; qq < wpr; ++qq) w += s_w[rr_][qq][mm];
+        st_stamped<T>(xw + W * (6 * (uint32_t)row0 + (uint32_t)t), w, stamp);
+        const double ui = (double)s_uo[t], ri = (double)s_ro[t];
+        g2 = ri * ui;
+        d2 = (double)w * ui;
+        q2 = ri * ri;
       }
       g2 = wave_sum(g2);
       d2 = wave_sum(d2);
       q2 = wave_sum(q2);
       if (one_wave) {
-        if (t == 0) {
-          double *pn2 = pd.part_cg[cu];
-          st_shared(pn2 + tile, g2);
-          st_shared(pn2 + nt + tile, d2);
-          st_shared(pn2 + 2 * nt + tile, q2);
-        }
-      } else if ((t & 63) == 0) {
-        s_red[3 * (t >> 6)] = g2;
-        s_red[3 * (t >> 6) + 1] = d2;
-        s_red[3 * (t >> 6) + 2] = q2;
+        st_partials(xp, nt, tile, g2, d2, q2, stamp);
+      } else if (lane == 0) {
+        s_red[3 * wv] = g2;
+        s_red[3 * wv + 1] = d2;
+        s_red[3 * wv + 2] = q2;
       }
     }
     if (!one_wave) {
       __syncthreads();
-      if (t == 0) {
-        double *pn2 = pd.part_cg[cu];
-        st_shared(pn2 + tile, s_red[0] + s_red[3] + s_red[6] + s_red[9]);
-        st_shared(pn2 + nt + tile, s_red[1] + s_red[4] + s_red[7] + s_red[10]);
-        st_shared(pn2 + 2 * nt + tile, s_red[2] + s_red[5] + s_red[8] + s_red[11]);
-      }
-    }
-    if (!grid_barrier(pd.cg_flag, nt, tile, (uint32_t)(it + 1), polls, s_flag + 1)) {
-      ok = false;
-      break;
+      if (wv == 0)
+        st_partials(xp, nt, tile, s_red[0] + s_red[3] + s_red[6] + s_red[9],
+                    s_red[1] + s_red[4] + s_red[7] + s_red[10], s_red[2] + s_red[5] + s_red[8] + s_red[11], stamp);
+      __syncthreads();
+      if (t < 3 * kPw) s_red[t] = 0.0;  // entries that no wave writes below stay zero
+      __syncthreads();
     }
   }
-  if (own) x[6 * (size_t)c + m] = xm;
+  if (polls <= 0) ok = false;  // no wait may succeed, also where the cap leaves none to make
+#pragma unroll
+  for (int k = 0; k < NS; ++k)
+    if (own[k] >= 0) x[ce[k]] = s_xo[own[k]];
+  if (tile == 0 && t == 0 && done_it >= 0) {
+    st->pcg_done = 1;
+    st->pcg_iters = done_it;
+  }
   if (!ok && t == 0) {
     st->pcg_fault = 1;
     st->pcg_done = 1;
@@ -2672,13 +2742,17 @@ struct CgStep {
       default: return (const void *)k_cg_step1<T, 0>;
     }
   }
-  static const void *resident(int R) {
+  template <int NS>
+  static const void *resident_sets(int R) {
     switch (R) {
-      case kPcgRows: return (const void *)k_cg_run<T, kPcgRows>;
-      case kPcgRowsSparse: return (const void *)k_cg_run<T, kPcgRowsSparse>;
-      case kPcgRowsMax: return (const void *)k_cg_run<T, kPcgRowsMax>;
-      default: return (const void *)k_cg_run<T, 0>;
+      case kPcgRows: return (const void *)k_cg_run<T, kPcgRows, NS>;
+      case kPcgRowsSparse: return (const void *)k_cg_run<T, kPcgRowsSparse, NS>;
+      default: return (const void *)k_cg_run<T, kPcgRowsMax, NS>;
     }
+  }
+  // the resident PCG for tiles of R rows whose longest column list is max_tcols
+  static const void *resident(int R, int max_tcols) {
+    return max_tcols > kCgSetCols ? resident_sets<2>(R) : resident_sets<1>(R);
   }
 };
 
@@ -4044,6 +4118,8 @@ struct Timed {
 // LDS available to the fused PCG form for z (bytes): the device's per-workgroup
 // limit less room for the kernel's static LDS, set once by prepare_kernels().
 static size_t g_fused_lds = 48 * 1024;
+// Whether the resident PCG may use its LDS on this device.
+static bool g_run_ok = false;
 // Per-workgroup LDS of the device (0 when the chunk form cannot be used).
 static size_t g_lds_limit = 0;
 // Whether the dense form's product kernel may use its LDS on this device.
@@ -4062,7 +4138,7 @@ int prepare_kernels() {
     bool ok = true;
     for (int R : {0, kPcgRows, kPcgRowsSparse, kPcgRowsMax})
       for (const void *f : {CgStep<float>::multi(R), CgStep<double>::multi(R), CgStep<float>::single(R),
-                            CgStep<double>::single(R), CgStep<float>::resident(R), CgStep<double>::resident(R)})
+                            CgStep<double>::single(R)})
         ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)use) == hipSuccess;
     if (!ok) {
       (void)hipGetLastError();
@@ -4070,6 +4146,17 @@ int prepare_kernels() {
     }
   }
   g_fused_lds = use;
+  // the resident PCG: the dynamic LDS of its longest column list
+  g_run_ok = true;
+  for (int R : {kPcgRows, kPcgRowsSparse, kPcgRowsMax})
+    for (int cols : {kCgSetCols, 2 * kCgSetCols})
+      for (int p = 0; p < 2; ++p)
+        if (hipFuncSetAttribute(p ? CgStep<float>::resident(R, cols) : CgStep<double>::resident(R, cols),
+                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)cg_run_lds_bytes(cols, p ? 4 : 8)) != hipSuccess) {
+          (void)hipGetLastError();
+          g_run_ok = false;
+        }
   g_lds_limit = lim > 0 ? (size_t)lim : 0;
   // the chunk form stages a chunk in up to chunk_lds_bytes of dynamic LDS
   const void *chunk_kernels[4] = {(const void *)k_schur_chunk<double, double>,
@@ -4121,10 +4208,10 @@ bool one_reduction_pcg(int precision, int max_tcols) {
 
 bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols) {
   if (prepare_kernels() != 0 || !one_reduction_pcg(precision, max_tcols)) return false;
-  if (6 * max_tcols > kCgColThreads || n_tiles < 1) return false;
-  const void *f = precision == 0 ? CgStep<double>::resident(rows) : CgStep<float>::resident(rows);
+  if (!g_run_ok || 6 * max_tcols > kCgColThreads || n_tiles < 1 || n_tiles > kCgRunTiles) return false;
+  const void *f =
+      precision == 0 ? CgStep<double>::resident(rows, max_tcols) : CgStep<float>::resident(rows, max_tcols);
   const size_t lds = cg_run_lds_bytes(max_tcols, precision == 0 ? 8 : 4);
-  if (lds > g_fused_lds) return false;
   int dev = 0, n_cu = 0, per_cu = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
@@ -4132,7 +4219,7 @@ bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols) {
     (void)hipGetLastError();
     return false;
   }
-  return (int64_t)n_tiles <= (int64_t)n_cu * per_cu;
+  return per_cu >= 1 && n_tiles <= n_cu;
 }
 
 template <class T, class S>
@@ -4216,7 +4303,7 @@ static hipError_t lm_iteration(const BatchPlan &bp, int pcg_max, int max_tcols, 
     Timed t(tm, K_PCG_CG, s, resident ? 1 : pcg_max);
     hipError_t le = hipSuccess;
     if (resident) {
-      const void *f = CgStep<T>::resident(bp.pcg_rows);
+      const void *f = CgStep<T>::resident(bp.pcg_rows, max_tcols);
       void *args[] = {(void *)&bp.single, (void *)&pcg_max};
       const unsigned lds = (unsigned)cg_run_lds_bytes(max_tcols, sizeof(T));
       // cooperative: the runtime places every workgroup at once or fails the launch;

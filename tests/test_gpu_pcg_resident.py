@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import ba_oracle as O
-from synth import make_config1, make_pose_graph, make_small_drive
+from synth import make_arc_scene, make_config1, make_pose_graph, make_small_drive
 
 pytestmark = pytest.mark.gpu
 
@@ -174,3 +174,19 @@ def test_pose_graph_sixteen_row_tiles_resident_equals_per_launch(balib, prec):
     assert np.array_equal(a["iter_cost"], b["iter_cost"])
     assert list(a["pcg_iters"]) == list(b["pcg_iters"])
     assert np.array_equal(a["q"], b["q"]) and np.array_equal(a["t"], b["t"])
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("case", ["columns", "tiles"])
+def test_resident_exchange_edges(balib, prec, case):
+    """Where the resident PCG's exchange changes form: 167 free cameras that all see each
+    other (more columns per tile than the 160 of one set) and a 700-camera drive (175
+    tiles: a thread takes two partial words); the last tile ragged in both.  The solve
+    repeats the per-launch one bit for bit."""
+    s = make_arc_scene(168, 1200, seed=9) if case == "columns" else make_small_drive(700, 14000, seed=8)
+    kw = dict(max_iters=4, pcg_max_iters=40, pcg_rel_tol=1e-10, precision=prec)
+    _, a = _run(balib, s, 0, **kw)
+    ib, b = _run(balib, s, RESIDENT, **kw)
+    _say("rows", ib["pcg_rows"], "resident", ib["pcg_resident"], "pcg", list(b["pcg_iters"]))
+    assert ib["pcg_resident"] == 1 and ib["pcg_rows"] == 4
+    _same(a, b)
