@@ -60,7 +60,7 @@ extern "C" {
 #define BA_STATUS_OK 0
 #define BA_STATUS_DAMPING 1    /* lambda ended at its upper clamp (1e16)     */
 #define BA_STATUS_NUMERICAL 2  /* the cost became non-finite                  */
-#define BA_STATUS_PCG_SYNC 3   /* the resident PCG's grid barrier timed out (its workgroups
+#define BA_STATUS_PCG_SYNC 3   /* a wait of the resident PCG timed out (its workgroups
                                   were not all resident at once): the solve stopped with the
                                   step rejected; solve without BA_FLAG_PCG_RESIDENT         */
 
@@ -102,16 +102,21 @@ typedef struct {
    wave per row) whatever the problem size, when the tile's columns fit in LDS.  By
    default that layout is used only for more than 8192 free cameras. */
 #define BA_FLAG_PCG_WIDE 8
-/* BA_FLAG_PCG_RESIDENT: run each linear solve of a single-problem solve as ONE launch
-   whose workgroups stay resident and meet at a grid barrier once per iteration, instead
-   of one launch per iteration: each workgroup keeps its S blocks and preconditioner rows
-   in registers for the whole solve, and no launch gaps remain.  The iterates are the
-   same, bit for bit.  Used when every workgroup of the solve fits on the device at once
-   (at most one 1024-thread workgroup per CU for 4-row tiles) and a tile's columns fit one
-   sweep (at most 170); otherwise ignored (ba_problem_info.pcg_resident reports it).  The
-   barrier needs the CUs to itself: do not run two such solves at the same time, nor
-   other long kernels beside one.  A barrier that times out (about a second) stops the
-   solve with status BA_STATUS_PCG_SYNC instead of waiting forever. */
+/* The PCG runs each linear solve as ONE launch wherever its workgroups can all be resident
+   at once: each keeps its S blocks in registers for the whole solve and the workgroups
+   hand each other the new products once per iteration, with bounded waits.  A solve takes
+   the compute units of its run out of a count the library keeps per device, so that
+   several solves (or servers) at once stay within the device; one that finds them taken
+   launches its PCG per iteration instead.  Where other work keeps a workgroup from
+   starting (for about 15 ms), one workgroup runs the linear solve alone, slowly.  All
+   three give the same iterates, bit for bit.
+   BA_FLAG_PCG_RESIDENT: run each linear solve of a single-problem solve as one launch in
+   any case, without that fall-back.  Used when every workgroup of the solve fits on the
+   device at once (at most one 1024-thread workgroup per CU for 4-row tiles) and a tile's
+   columns fit one sweep (at most 170); otherwise ignored (ba_problem_info.pcg_resident
+   reports it).  The run needs the CUs to itself: do not run two such solves at the same
+   time, nor other long kernels beside one.  A wait that times out (about a second) stops
+   the solve with status BA_STATUS_PCG_SYNC instead of waiting forever. */
 #define BA_FLAG_PCG_RESIDENT 16
 /* BA_FLAG_PCG_COOPERATIVE: with BA_FLAG_PCG_RESIDENT, start the resident solve as a
    cooperative launch, so the runtime itself places every workgroup at once (or fails the
@@ -307,12 +312,14 @@ void ba_destroy(ba_problem *p);
    LM iteration replays three graphs (before, during and after the PCG run)
    with the events between them. */
 int ba_set_profiling(ba_problem *p, int32_t mask, int32_t stride);
-/* Test hook for the time-out path of BA_FLAG_PCG_RESIDENT: the number of polls of the
-   other workgroups' flags after which the resident PCG's grid barrier gives up
-   (default 1048576, about a second).  With 0 every barrier gives up at once, so every
-   workgroup of the launch exits at its first barrier, the LM iteration rejects its
-   step, and the solve ends with status BA_STATUS_PCG_SYNC and iters = that
-   iteration's number.  Applies from the next solve on; BA_EINVAL for polls < 0. */
+/* Test hook for the time-out paths of the one-launch PCG: the number of polls of the other
+   workgroups' values after which a wait gives up (default 1048576, about a second).  With
+   BA_FLAG_PCG_RESIDENT and 0 every wait gives up at once, so every workgroup of the launch
+   exits at its first wait, the LM iteration rejects its step, and the solve ends with
+   status BA_STATUS_PCG_SYNC and iters = that iteration's number.  Without the flag the
+   bound applies to the first wait of each linear solve (at most about 15 ms), and 0 makes
+   one workgroup run every linear solve.  Applies from the next solve on; BA_EINVAL for
+   polls < 0. */
 int ba_set_barrier_polls(ba_problem *p, int32_t polls);
 /* Test export of one LM iteration's intermediate quantities, for element-wise
    checks of the linearisation, the Schur complement (paper Sec. 4.3; the reduced

@@ -17,7 +17,9 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <map>
 #include <memory>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -714,6 +716,7 @@ int analyse(const ba_problem_desc *d, const ba_options *opt, Symbolic &sy, const
   sy.pcg_resident = (opt->flags & BA_FLAG_PCG_RESIDENT) &&
                     resident_pcg_fits(prec, sy.pcg_rows, (Cf + sy.pcg_rows - 1) / sy.pcg_rows, sy.max_tcols);
   sy.pcg_coop = sy.pcg_resident && (opt->flags & BA_FLAG_PCG_COOPERATIVE);
+  sy.pcg_run = falling_back_pcg(prec, sy.pcg_rows, (Cf + sy.pcg_rows - 1) / sy.pcg_rows, sy.max_tcols);
   if (sy.dense) {
     // first record of each point in each camera tile: the point's records in the tile
     // are the range [ts[t], ts[t + 1]) (records are point-major, in camera order), and
@@ -891,6 +894,7 @@ size_t DevProblem::plan(const Symbolic &sy, int precision, int max_iters, Offset
     o.cg_xw[b] = L.take(Cf * 6 * (T / 4) * 8);
     o.cg_xp[b] = L.take(npcg * 6 * 8);
   }
+  o.cg_dec = L.take(4);
   o.part_rr = L.take(npcg * 8);
   o.part_cull = L.take(npt * 8);
   o.iter_cost = rep + RL.ic;
@@ -1059,6 +1063,7 @@ int DevProblem::init(const Symbolic &sy, const ba_problem_desc *d, const ba_opti
     pd.cg_xw[b] = (uint64_t *)ptr(off.cg_xw[b]);
     pd.cg_xp[b] = (uint64_t *)ptr(off.cg_xp[b]);
   }
+  pd.cg_dec = (uint32_t *)ptr(off.cg_dec);
   pd.part_rr = (double *)ptr(off.part_rr);
   pd.part_cull = (int32_t *)ptr(off.part_cull);
   pd.st = (LMState *)ptr(off.st);
@@ -1341,6 +1346,24 @@ struct RigPart {
   }
 };
 
+namespace bax {
+namespace {
+std::mutex g_cus_mu;
+std::map<int, int> g_cus_used;
+}  // namespace
+bool take_cus(int device, int n, bool always) {
+  std::lock_guard<std::mutex> lk(g_cus_mu);
+  int &used = g_cus_used[device];
+  if (!always && used + n > device_cus()) return false;
+  used += n;
+  return true;
+}
+void give_cus(int device, int n) {
+  std::lock_guard<std::mutex> lk(g_cus_mu);
+  g_cus_used[device] -= n;
+}
+}  // namespace bax
+
 struct ba_problem {
   Symbolic sy;
   DevProblem dp;
@@ -1357,18 +1380,36 @@ struct ba_problem {
   bool solved = false;
   bool profiling = false;
   bool use_graph = true;
-  hipGraph_t graph = nullptr;       // the launch sequence of one solve, captured once
-  hipGraphExec_t graph_exec = nullptr;
+  // the launch sequence of one solve, captured once: with the PCG as this problem runs it,
+  // and launched per iteration, for when the one-launch run's CUs are taken
+  hipGraph_t graph[2] = {};
+  hipGraphExec_t graph_exec[2] = {};
+  int device = 0;  // the device the problem lives on
+  int cus = 0;     // CUs taken for the one-launch PCG of the solve in flight
   // the LM iterations around their PCG runs: before the first run, the run, after a run and
   // before the next one, after the last run
   hipGraph_t seg_graph[4] = {};
   hipGraphExec_t seg_exec[4] = {};
+  bool seg_one = false;  // the segment graphs were captured around one-launch runs
   EventTimer timer;  // times the kernels selected by timer.mask
   double kernel_ms[K_NUM_KERNELS] = {};
   int32_t kernel_launches[K_NUM_KERNELS] = {};
   double solve_ms = 0.0;
   char *rep_pin = nullptr;  // page-locked: the fresh state's upload slot and the report block
   bool rep_ok = false;      // rep_pin holds the last solve's report
+
+  void give_back_cus() {
+    if (cus) bax::give_cus(device, cus);
+    cus = 0;
+  }
+  void drop_segments() {
+    for (int i = 0; i < 4; ++i) {
+      if (seg_exec[i]) (void)hipGraphExecDestroy(seg_exec[i]);
+      if (seg_graph[i]) (void)hipGraphDestroy(seg_graph[i]);
+      seg_exec[i] = nullptr;
+      seg_graph[i] = nullptr;
+    }
+  }
 };
 
 extern "C" {
@@ -1401,6 +1442,7 @@ static int create_problem(const ba_problem_desc *d, const ba_options *opt, void 
   if (prepare_kernels() != 0) return fail(BA_EDEVICE, "no HIP device");
   p->bytes = DevProblem::bytes_for(p->sy, opt->precision, opt->max_iters);
   p->use_graph = (opt->flags & BA_FLAG_NO_GRAPH) == 0;
+  (void)hipGetDevice(&p->device);
   if (hip_stream) {
     p->stream = (hipStream_t)hip_stream;
   } else {
@@ -1820,9 +1862,10 @@ int ba_pose_graph_create(const ba_pose_graph_desc *g, const ba_options *opt, voi
   return create_problem(&d, opt, hip_stream, &ge, out);
 }
 
-int ba_solve_async(ba_problem *p) {
-  if (!p) return fail(BA_EINVAL, "problem is NULL");
-  if (p->pending) return fail(BA_ESTATE, "a solve is already in flight");
+}  // extern "C"
+
+// Queues a solve; one: its PCG runs in one launch.
+static int queue_solve(ba_problem *p, const bool one) {
   p->rep_ok = false;
   if (!p->rep_pin) {
     hipError_t ea = hipHostMalloc((void **)&p->rep_pin, p->dp.report_bytes(), hipHostMallocDefault);
@@ -1842,7 +1885,9 @@ int ba_solve_async(ba_problem *p) {
     // same launch sequence serves every solve: capture it once and replay it.
     // (Per-kernel timing needs events between launches: profiled solves are
     // enqueued kernel by kernel instead.)
-    if (!p->graph_exec) {
+    hipGraph_t &graph = p->graph[one ? 0 : 1];
+    hipGraphExec_t &graph_exec = p->graph_exec[one ? 0 : 1];
+    if (!graph_exec) {
       e = hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal);
       if (e != hipSuccess) return hip_fail(e, "graph capture");
       hipError_t el = hipSuccess;
@@ -1851,14 +1896,14 @@ int ba_solve_async(ba_problem *p) {
                                            p->rig->sy.max_tcols, p->stream, nullptr)
                     : launch_lm_iteration(p->dp.precision, p->batch.plan, p->dp.pcg_max, p->dp.max_tcols,
                                           p->stream, nullptr);
-      e = hipStreamEndCapture(p->stream, &p->graph);
+      e = hipStreamEndCapture(p->stream, &graph);
       if (el != hipSuccess) return hip_fail(el, "kernel launch during capture");
       if (e != hipSuccess) return hip_fail(e, "graph capture");
-      e = hipGraphInstantiate(&p->graph_exec, p->graph, nullptr, nullptr, 0);
+      e = hipGraphInstantiate(&graph_exec, graph, nullptr, nullptr, 0);
       if (e != hipSuccess) return hip_fail(e, "graph instantiate");
     }
     (void)hipEventRecord(p->ev0, p->stream);
-    e = hipGraphLaunch(p->graph_exec, p->stream);
+    e = hipGraphLaunch(graph_exec, p->stream);
     if (e != hipSuccess) return hip_fail(e, "graph launch");
     (void)hipEventRecord(p->ev1, p->stream);
     // the final evaluation stays outside the graph and is not timed
@@ -1873,6 +1918,8 @@ int ba_solve_async(ba_problem *p) {
     // Only the PCG run is timed: the solve is replayed as graphs between the PCG runs
     // (their launches are the same in every iteration), with the timing events around
     // each run: two graph launches per LM iteration.
+    if (p->seg_exec[0] && p->seg_one != one) p->drop_segments();
+    p->seg_one = one;
     if (!p->seg_exec[0]) {
       for (int part = 0; part < 4; ++part) {
         e = hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal);
@@ -1896,9 +1943,9 @@ int ba_solve_async(ba_problem *p) {
     (void)hipEventRecord(p->ev0, p->stream);
     if (p->dp.max_iters > 0) e = hipGraphLaunch(p->seg_exec[0], p->stream);
     for (int it = 0; it < p->dp.max_iters && e == hipSuccess; ++it) {
-      p->timer.begin(K_PCG_CG, p->stream, p->sy.pcg_resident ? 1 : p->dp.pcg_max);
+      p->timer.begin(K_PCG_CG, p->stream, one ? 1 : p->dp.pcg_max);
       // the resident run is one kernel: launched directly, not as a one-node graph
-      e = p->sy.pcg_resident ? launch_lm_iteration(p->dp.precision, p->batch.plan, p->dp.pcg_max, p->dp.max_tcols,
+      e = one ? launch_lm_iteration(p->dp.precision, p->batch.plan, p->dp.pcg_max, p->dp.max_tcols,
                                                    p->stream, nullptr, LM_PCG)
                              : hipGraphLaunch(p->seg_exec[1], p->stream);
       p->timer.end(K_PCG_CG, p->stream);
@@ -1924,11 +1971,34 @@ int ba_solve_async(ba_problem *p) {
   return BA_OK;
 }
 
+extern "C" {
+
+int ba_solve_async(ba_problem *p) {
+  if (!p) return fail(BA_EINVAL, "problem is NULL");
+  if (p->pending) return fail(BA_ESTATE, "a solve is already in flight");
+  // the linear solves run in one launch each where their tiles fit the device beside the
+  // other such runs in flight (asked for by flag: in any case), else per iteration
+  const Symbolic &sy = p->rig ? p->rig->sy : p->sy;
+  const bool flagged = !p->rig && sy.pcg_resident;
+  const int per_wg = flagged ? 1 : sy.pcg_run;
+  const int n = per_wg ? ((sy.Cf + sy.pcg_rows - 1) / sy.pcg_rows + per_wg - 1) / per_wg : 0;
+  const bool one = n > 0 && take_cus(p->device, n, flagged);
+  if (one) p->cus = n;
+  (p->rig ? p->rig->batch : p->batch).plan.pcg_run = one ? per_wg : 0;
+  const int rc = queue_solve(p, one);
+  if (rc != BA_OK) {
+    if (one) (void)hipStreamSynchronize(p->stream);  // whatever was queued before the error
+    p->give_back_cus();
+  }
+  return rc;
+}
+
 int ba_wait(ba_problem *p) {
   if (!p) return fail(BA_EINVAL, "problem is NULL");
   if (!p->pending) return BA_OK;
   hipError_t e = hipStreamSynchronize(p->stream);
   p->pending = false;
+  p->give_back_cus();
   if (e != hipSuccess) return hip_fail(e, "solve");
   float ms = 0.0f;
   (void)hipEventElapsedTime(&ms, p->ev0, p->ev1);
@@ -2239,12 +2309,12 @@ int64_t ba_problem_bytes(const ba_problem *p) { return p ? (int64_t)p->bytes : 0
 void ba_destroy(ba_problem *p) {
   if (!p) return;
   if (p->pending) (void)hipStreamSynchronize(p->stream);
-  if (p->graph_exec) (void)hipGraphExecDestroy(p->graph_exec);
-  if (p->graph) (void)hipGraphDestroy(p->graph);
-  for (int i = 0; i < 4; ++i) {
-    if (p->seg_exec[i]) (void)hipGraphExecDestroy(p->seg_exec[i]);
-    if (p->seg_graph[i]) (void)hipGraphDestroy(p->seg_graph[i]);
+  p->give_back_cus();
+  for (int i = 0; i < 2; ++i) {
+    if (p->graph_exec[i]) (void)hipGraphExecDestroy(p->graph_exec[i]);
+    if (p->graph[i]) (void)hipGraphDestroy(p->graph[i]);
   }
+  p->drop_segments();
   if (p->mem) (void)hipFree(p->mem);
   if (p->ev0) (void)hipEventDestroy(p->ev0);
   if (p->ev1) (void)hipEventDestroy(p->ev1);
@@ -2279,6 +2349,7 @@ int ba_debug_iteration_export(ba_problem *p, ba_debug_iteration *out) {
   dp.pending_state = dp.fresh_state();
   dp.pending_state.max_iters = 1;
   hipError_t e = hipMemcpyAsync(v.st, &dp.pending_state, sizeof(LMState), hipMemcpyHostToDevice, p->stream);
+  p->batch.plan.pcg_run = 0;
   if (e == hipSuccess) e = launch_lm_iteration(dp.precision, p->batch.plan, dp.pcg_max, dp.max_tcols, p->stream, nullptr);
   if (e == hipSuccess) e = launch_eval(dp.precision, p->batch.plan, p->stream, nullptr);
   double *dev = nullptr;  // records widened to FP64: r (2), J_c (12), J_p (6) per observation

@@ -223,6 +223,7 @@ struct ProbDev {
   double *part_pq;                // [n_pcg_tiles]
   double *part_cg[2];             // [3][n_pcg_tiles] r.u, w.u, r.r partials by parity
   uint64_t *cg_xw[2];             // [6 Cf][words of T] resident PCG: stamped w by parity (see k_cg_run)
+  uint32_t *cg_dec;               // resident PCG that may fall back: the decision word
   uint64_t *cg_xp[2];             // [6][n_pcg_tiles] ... stamped words of the r.u, w.u, r.r partials
   double *part_rr;                // [n_pcg_tiles]
   int32_t *part_cull;             // [n_pt_tiles][2] active observations, points with one, after culling
@@ -242,6 +243,8 @@ struct BatchPlan {
   int32_t n_dpt, n_dcm, n_dsy, n_dre;
   int32_t n_probs;
   int32_t pcg_rows;  // rows per PCG tile shared by every problem of the batch, 0 if mixed
+  int32_t pcg_run;   // the PCG in one launch that falls back to one workgroup when its tiles
+                     // cannot all run at once: tiles per workgroup, 0: a launch per iteration
   ProbDev single;  // host copy of the descriptor when n_probs == 1 (passed by value to short kernels)
 };
 
@@ -294,6 +297,11 @@ bool one_reduction_pcg(int precision, int max_tcols);
 // True when the resident PCG (one launch, grid barriers) can run a problem: every
 // tile's columns fit one sweep and all n_tiles workgroups can be resident at once.
 bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols);
+// CUs of the current device (0: none present).
+int device_cus();
+// Tiles per workgroup (1 or 2) of the PCG in one launch that falls back (BatchPlan::pcg_run)
+// for a problem of n_tiles tiles; 0 where it does not fit.
+int falling_back_pcg(int precision, int rows, int n_tiles, int max_tcols);
 // Parts of one LM iteration: everything, or the launches before the PCG run, the
 // PCG run itself, and the launches after it (so the run can be timed between graphs).
 enum LmPart { LM_ALL = 0, LM_BEFORE_PCG, LM_PCG, LM_AFTER_PCG };

@@ -1939,6 +1939,7 @@ __global__ __launch_bounds__(64 * NW) void k_cg_start(const ProbDev *__restrict_
     const int ne = 6 * cg_words<T>() * (min(pd.Cf, (tl.idx + 1) * pd.pcg_rows) - tl.idx * pd.pcg_rows);
     for (int k = threadIdx.x; k < ne; k += 64 * NW)
       for (int b = 0; b < 2; ++b) pd.cg_xw[b][e0 + k] = 0u;
+    if (tl.idx == 0 && threadIdx.x == 0) *pd.cg_dec = 0u;
     if (threadIdx.x < 12) pd.cg_xp[threadIdx.x / 6][(size_t)(threadIdx.x % 6) * pd.n_pcg_tiles + tl.idx] = 0u;
   }
   if (threadIdx.x == 0) s_flag[0] = lm_active(st) ? 1 : 0;
@@ -2409,8 +2410,8 @@ __device__ __forceinline__ T stamped_value(const uint64_t *v) {
   return o;
 }
 
-// The whole one-reduction PCG of one problem in one launch, for a grid whose tiles are
-// all resident at once (checked by the host): the same iterates in the same order as
+// The whole one-reduction PCG of a problem in one launch, for a grid whose tiles are
+// all resident at once (counted by the host): the same iterates in the same order as
 // pcg_max launches of k_cg_step1, with the exchange above where a launch boundary was.
 // What a launch re-read every iteration stays on chip for the whole solve: the tile's
 // S blocks in registers (those a lane group holds; longer rows read the rest each
@@ -2421,7 +2422,13 @@ __device__ __forceinline__ T stamped_value(const uint64_t *v) {
 // with more than 160 columns takes a second set of ten per wave (NS = 2).
 // Against the grid-barrier form, which exchanged w, s and r, read by all six lanes of a
 // column, an iteration of the 500-camera drive (2.3M observations) went from 8.4 to
-// 3.7 us.
+// 3.7 us; against a launch per iteration, the 203-camera submap went from 8.5 to 3.7 us, a
+// 24-camera window from 6.1 to 3.3, the 9000-node pose graph from 13.8 to 5.6 and the
+// 3000-camera loop from 25 (with the launches that find the solve converged) to 15.
+// Unless the caller asked for the run by flag, it falls back (fall_back): all tiles must
+// have published their first products within kCgGatherPolls polls; otherwise one word,
+// set by the first tile to give up or to finish, sends every tile out before it has
+// changed anything, and tile 0 runs the per-launch steps of all tiles by itself.
 constexpr int kCgRunTiles = 320;                                  // tiles at most
 constexpr int kCgRunFew = 16;                                      // up to which polls do not get in each other's way
 constexpr int kCgWaveCols = 10;                                   // columns per wave and set
@@ -2431,38 +2438,73 @@ constexpr int kCgSetCols = kCgWaveCols * (kCgThreads / 64);      // 160
 template <class T, int R, int NS>
 constexpr int cg_run_pre() {
   if (sizeof(T) == 8) return NS == 1 && R != kPcgRowsSparse ? 2 : 1;
-  return R == kPcgRows ? 4 : R == kPcgRowsMax ? (NS == 1 ? 4 : 3) : (NS == 1 ? 6 : 4);
+  return R == kPcgRows ? 4 : R == kPcgRowsMax ? (NS == 1 ? 4 : 3) : (NS == 1 ? 5 : 3);
 }
+// ... and blocks beyond those that are loaded together
+template <class T, int R>
+constexpr int cg_run_more() { return sizeof(T) == 4 && R == kPcgRowsSparse ? 4 : 1; }
 
 // Dynamic LDS of k_cg_run: u of the tile's columns, then each thread's M^-1 rows (FP64).
-__host__ __device__ constexpr size_t cg_run_mrow_offset(int max_tcols, size_t tbytes) {
-  return (6 * (size_t)max_tcols * tbytes + 7) / 8;  // in doubles
+__host__ __device__ constexpr size_t cg_run_mrow_offset(int cols, size_t tbytes) {
+  return (6 * (size_t)cols * tbytes + 7) / 8;  // in doubles
 }
-size_t cg_run_lds_bytes(int max_tcols, size_t tbytes) {
-  return 8 * cg_run_mrow_offset(max_tcols, tbytes) +
-         6 * sizeof(double) * kCgThreads * (max_tcols > kCgSetCols ? 2 : 1);
+size_t cg_run_lds_bytes(int max_tcols, size_t tbytes, int per_wg) {
+  return 8 * cg_run_mrow_offset(per_wg * max_tcols, tbytes) +
+         6 * sizeof(double) * kCgThreads * (per_wg == 2 || max_tcols > kCgSetCols ? 2 : 1);
 }
 
-template <class T, int R, int NS>
-__global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
+// The word by which a grid of a falling-back run agrees whether all its tiles take part
+// (kCgGo) or tile 0 alone (kCgSolo): the first decision stands.  Returns the standing one.
+constexpr uint32_t kCgGo = 1, kCgSolo = 2;
+__device__ __forceinline__ uint32_t cg_decide(global_t<uint32_t> *dec, uint32_t mine) {
+  uint32_t was = 0;
+  __hip_atomic_compare_exchange_strong(dec, &was, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return (uint32_t)__builtin_amdgcn_readfirstlane((int)(was ? was : mine));
+}
+__device__ __forceinline__ uint32_t cg_decision(global_t<uint32_t> *dec) {
+  return (uint32_t)__builtin_amdgcn_readfirstlane(
+      (int)__hip_atomic_load(dec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+// Polls of the first exchange after which a falling-back run takes it that some tile is
+// not running (about 15 ms: longer than kernels that merely have the CUs first).
+constexpr int kCgGatherPolls = 1 << 14;
+
+// The PCG of one problem by one workgroup: the per-launch steps of all tiles, one after
+// another (out of line: its registers are not the run's).
+template <class T, int R>
+__device__ __noinline__ void cg_solo(const ProbDev *pd, int n_iter) {
+  for (int it = 0; it < n_iter; ++it)
+    for (int k = 0; k < pd->n_pcg_tiles; ++k) {
+      __syncthreads();
+      cg_step_body<T, R>(*pd, k, it);
+    }
+}
+
+// Workgroup wg runs tiles TP wg .. TP wg + TP - 1; with TP = 2 the second column set holds
+// the second tile's columns.  dpd: the descriptor in device memory (pd may be a kernel
+// argument).
+template <class T, int R, int NS, int TP>
+__device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dpd, const int wg, int n_iter,
+                                            const bool fall_back) {
+  static_assert(TP == 1 || NS == TP, "one column set per tile");
   extern __shared__ double s_dyn[];
   T *ul = (T *)s_dyn;  // [tile columns][6]: u_{it+1} of every column this tile reads
   // [set][thread][6] M^-1 rows (in LDS: the S blocks fill the registers)
-  double *ml = s_dyn + cg_run_mrow_offset(pd.max_tcols, sizeof(T));
+  double *ml = s_dyn + cg_run_mrow_offset(TP * pd.max_tcols, sizeof(T));
   constexpr int kPw = (kCgRunTiles + 63) / 64;  // waves that sum the tiles' partials
   __shared__ double s_pd[3][kCgRunTiles];       // r.u, w.u, r.r partials of every tile
   __shared__ double s_red[3 * kPw];
-  __shared__ T s_w[R][4][6];
-  __shared__ T s_ro[6 * R], s_uo[6 * R], s_po[6 * R], s_xo[6 * R];  // r, u, p, x of the own rows
+  __shared__ double s_fin[3 * TP * ((6 * R + 63) / 64)];
+  constexpr int kWr = R == kPcgRows ? 4 : 1;    // waves per row (a half-wave row counts as one)
+  __shared__ T s_w[TP * R][kWr][6];
+  __shared__ T s_ro[TP * 6 * R], s_uo[TP * 6 * R], s_po[TP * 6 * R], s_xo[TP * 6 * R];  // r, u, p, x of the own rows
   __shared__ int s_flag[2];
-  const int tile = blockIdx.x;
   LMState *st = pd.st;
   const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int nt = pd.n_pcg_tiles;
   constexpr int Lr = kCgThreads / R;            // lanes per row
-  constexpr int wpr = Lr >= 64 ? Lr / 64 : 1;  // waves per row
   constexpr uint32_t W = cg_words<T>();
-  const int row0 = tile * R, row1 = min(pd.Cf, row0 + R);
+  const int Cf = pd.Cf, row0 = wg * TP * R, row1 = min(Cf, row0 + TP * R);
   const int ncmax = pd.max_tcols;
   const auto S = as_global((const T *)pd.S);
   const auto S_lcol = as_global(pd.S_lcol);
@@ -2476,7 +2518,8 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
   if (!s_flag[0]) return;
   n_iter = min(n_iter, st->pcg_max);
   const double tol = st->pcg_tol, bb = st->pcg_bb;
-  const int polls = st->bar_polls;
+  const int polls = fall_back ? min(st->bar_polls, kCgGatherPolls) : st->bar_polls;
+  const auto dec = as_global(pd.cg_dec);
   // ---- per-solve constants and the state of the tile's columns and own rows
   const bool col_lane = lane < 6 * kCgWaveCols;
   const int cg = col_lane ? lane / 6 : kCgWaveCols - 1, m = col_lane ? lane - 6 * cg : 0;
@@ -2485,10 +2528,10 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
   T wc[NS], sc[NS], rc[NS];  // w, s and r of the column's element
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
-    const int lc = kCgSetCols * k + kCgWaveCols * wv + cg;
-    const int cc = col_lane && lc < ncmax ? as_global(pd.tcol)[(size_t)tile * ncmax + lc] : -1;
-    ulo[k] = cc >= 0 ? 6 * lc + m : -1;
-    own[k] = cc >= row0 && cc < row1 ? 6 * (cc - row0) + m : -1;
+    const int lc = (TP == 1 ? kCgSetCols * k : 0) + kCgWaveCols * wv + cg, tile = wg * TP + (TP == 1 ? 0 : k);
+    const int cc = col_lane && lc < ncmax && tile < nt ? as_global(pd.tcol)[(size_t)tile * ncmax + lc] : -1;
+    ulo[k] = cc >= 0 ? 6 * (lc + (TP == 1 ? 0 : k * ncmax)) + m : -1;
+    own[k] = cc >= tile * R && cc < min(Cf, (tile + 1) * R) ? 6 * (cc - row0) + m : -1;
     const int c = cc >= 0 ? cc : row0;
     ce[k] = 6 * (uint32_t)c + (uint32_t)m;
     wc[k] = as_global((const T *)pd.cg_w[0])[ce[k]];
@@ -2508,24 +2551,28 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
   const int hs = Lr >= 64 ? (h & 63) : h;
   constexpr int gps = Lr >= 64 ? 10 : 5;
   const int g = hs / 6, i = hs - 6 * (hs / 6);
-  const int a = row0 + rw;
-  constexpr int bstep = gps * wpr;
-  int b0 = 0, b1 = 0;
-  if (g < gps && a < row1) {
-    b0 = as_global(pd.S_rowptr)[a] + gps * q + g;
-    b1 = as_global(pd.S_rowptr)[a + 1];
-  }
-  constexpr int kPre = cg_run_pre<T, R, NS>();
-  T sreg[kPre][6];
-  int lreg[kPre];  // the block's column in ul (a block the lane does not have: 0 times column 0)
+  constexpr int bstep = gps * kWr;
+  int b0[TP], b1[TP];
 #pragma unroll
-  for (int k = 0; k < kPre; ++k) {
-    const int blk = b0 + bstep * k;
-    const bool has = blk < b1;
-    lreg[k] = has ? 6 * S_lcol[blk] : -1;
-#pragma unroll
-    for (int n = 0; n < 6; ++n) sreg[k][n] = has ? S[36 * (size_t)blk + 6 * i + n] : T(0);
+  for (int p = 0; p < TP; ++p) {
+    const int a = row0 + p * R + rw;
+    const bool has = g < gps && a < Cf;
+    b0[p] = has ? as_global(pd.S_rowptr)[a] + gps * q + g : 0;
+    b1[p] = has ? as_global(pd.S_rowptr)[a + 1] : 0;
   }
+  constexpr int kPre = cg_run_pre<T, R, NS>() / TP, kMore = cg_run_more<T, R>();
+  T sreg[TP][kPre][6];
+  int lreg[TP][kPre];  // the block's column in ul, -1 for a block the lane does not have
+#pragma unroll
+  for (int p = 0; p < TP; ++p)
+#pragma unroll
+    for (int k = 0; k < kPre; ++k) {
+      const int blk = b0[p] + bstep * k;
+      const bool has = blk < b1[p];
+      lreg[p][k] = has ? 6 * (S_lcol[blk] + p * ncmax) : -1;
+#pragma unroll
+      for (int n = 0; n < 6; ++n) sreg[p][k][n] = has ? S[36 * (size_t)blk + 6 * i + n] : T(0);
+    }
   // this thread's share of the tiles' partial words (word j of tile k at j * nt + k) and
   // where they go in s_pd; then the waves that sum them (thread k: tile k, as in the
   // per-launch step)
@@ -2556,7 +2603,17 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
       else __builtin_amdgcn_s_sleep(10);
       bool all = false;
       uint64_t xv[NS][W], pv[2];
-      for (int n = 0; n < polls && !all; ++n) {
+      bool lost = false;
+      for (int n = 0; !all && !lost; ++n) {
+        if (fall_back && n >= polls && it == 1) {
+          // not every tile is running: one word decides for the whole grid
+          lost = cg_decide(dec, kCgSolo) == kCgSolo;
+          if (lost) break;
+        } else if (n >= (fall_back ? kBarPollsDefault : polls)) {
+          break;
+        } else if (fall_back && (n & 255) == 255) {
+          lost = cg_decision(dec) == kCgSolo;
+        }
 #pragma unroll
         for (int k = 0; k < NS; ++k)
 #pragma unroll
@@ -2577,7 +2634,7 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
         ((uint32_t *)&s_pd[0][0])[pl[0]] = (uint32_t)pv[0];
         if (two_words) ((uint32_t *)&s_pd[0][0])[pl[1]] = (uint32_t)pv[1];
       }
-      if (!all && lane == 0) s_flag[1] = 1;
+      if (!all && lane == 0) s_flag[1] = lost ? 2 : 1;
     }
     __syncthreads();
     if (sums) {
@@ -2598,7 +2655,7 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
     }
     __syncthreads();
     if (s_flag[1]) {
-      ok = false;
+      ok = s_flag[1] == 2;
       break;
     }
     double gam = s_red[0], del = s_red[kPw], rr = s_red[2 * kPw];
@@ -2650,39 +2707,55 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
     if (it + 1 == n_iter) break;  // the last x is formed: no tile reads a further product
     __syncthreads();
     // ---- w_{it+1} = S u_{it+1} for the tile's rows
-    T acc = T(0);
 #pragma unroll
-    for (int k = 0; k < kPre; ++k)
-      if (lreg[k] >= 0) {
-        const T *uc = ul + lreg[k];
+    for (int p = 0; p < TP; ++p) {
+      T acc = T(0);
 #pragma unroll
-        for (int n = 0; n < 6; ++n) acc += sreg[k][n] * uc[n];
+      for (int k = 0; k < kPre; ++k)
+        if (lreg[p][k] >= 0) {
+          const T *uc = ul + lreg[p][k];
+#pragma unroll
+          for (int n = 0; n < 6; ++n) acc += sreg[p][k][n] * uc[n];
+        }
+      for (int blk = b0[p] + bstep * kPre; blk < b1[p]; blk += bstep * kMore) {  // loads together, sums in order
+        T sv[kMore][6];
+        int lv[kMore];
+#pragma unroll
+        for (int k = 0; k < kMore; ++k) {
+          const int bk = min(blk + bstep * k, b1[p] - 1);
+          lv[k] = 6 * (S_lcol[bk] + p * ncmax);
+#pragma unroll
+          for (int n = 0; n < 6; ++n) sv[k][n] = S[36 * (size_t)bk + 6 * i + n];
+        }
+#pragma unroll
+        for (int k = 0; k < kMore; ++k)
+          if (blk + bstep * k < b1[p]) {
+#pragma unroll
+            for (int n = 0; n < 6; ++n) acc += sv[k][n] * ul[lv[k] + n];
+          }
       }
-    for (int blk = b0 + bstep * kPre; blk < b1; blk += bstep) {
-      const auto Srow = S + 36 * (size_t)blk + 6 * i;
-      const T *uc = ul + 6 * S_lcol[blk];
-#pragma unroll
-      for (int n = 0; n < 6; ++n) acc += Srow[n] * uc[n];
+      // the group sums in group order, in the lanes of the row's first group
+      const T wi = lane_stride_sum<gps, 6>(Lr >= 64 ? 4 * i : 4 * ((t & 32) + i), acc);
+      if (hs < 6) s_w[p * R + rw][q][hs] = wi;
     }
-    // the group sums in group order, in the lanes of the row's first group
-    const T wi = lane_stride_sum<gps, 6>(Lr >= 64 ? 4 * i : 4 * ((t & 32) + i), acc);
-    if (hs < 6 && a < row1) s_w[rw][q][hs] = wi;
     __syncthreads();
     // ---- w_{it+1} of the tile's rows and its partials of gamma_{it+1}, delta_{it+1},
     // ||r_{it+1}||^2 (as the per-launch step: wave 0 alone when 6 R <= 64)
-    constexpr bool one_wave = 6 * R <= 64;
+    // (FW waves per tile; as the per-launch step sums its waves, in order)
+    constexpr int FW = (6 * R + 63) / 64;
     const auto xw = (it & 1) ? xw0 : xw1;
     const auto xp = (it & 1) ? xp0 : xp1;
     const uint32_t stamp = (uint32_t)it + 1;
-    if (one_wave ? wv == 0 : wv < 4) {
+    if (wv < TP * FW) {
       double g2 = 0.0, d2 = 0.0, q2 = 0.0;
-      if (t < 6 * (row1 - row0)) {
-        const int rr_ = t / 6, mm = t - 6 * (t / 6);
+      const int e = t - (TP == 1 ? 0 : 64 * FW * (wv / FW)), eo = e + (TP == 1 ? 0 : 6 * R * (wv / FW));
+      if (e < 6 * R && eo < 6 * (row1 - row0)) {
+        const int rr_ = eo / 6, mm = eo - 6 * (eo / 6);
         T w = s_w[rr_][0][mm];
 #pragma unroll
-        for (int qq = 1; qq < wpr; ++qq) w += s_w[rr_][qq][mm];
-        st_stamped<T>(xw + W * (6 * (uint32_t)row0 + (uint32_t)t), w, stamp);
-        const double ui = (double)s_uo[t], ri = (double)s_ro[t];
+        for (int qq = 1; qq < kWr; ++qq) w += s_w[rr_][qq][mm];
+        st_stamped<T>(xw + W * (6 * (uint32_t)row0 + (uint32_t)eo), w, stamp);
+        const double ui = (double)s_uo[eo], ri = (double)s_ro[eo];
         g2 = ri * ui;
         d2 = (double)w * ui;
         q2 = ri * ri;
@@ -2690,29 +2763,46 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
       g2 = wave_sum(g2);
       d2 = wave_sum(d2);
       q2 = wave_sum(q2);
-      if (one_wave) {
-        st_partials(xp, nt, tile, g2, d2, q2, stamp);
+      if (FW == 1) {
+        st_partials(xp, nt, wg, g2, d2, q2, stamp);
       } else if (lane == 0) {
-        s_red[3 * wv] = g2;
-        s_red[3 * wv + 1] = d2;
-        s_red[3 * wv + 2] = q2;
+        s_fin[3 * wv] = g2;
+        s_fin[3 * wv + 1] = d2;
+        s_fin[3 * wv + 2] = q2;
       }
     }
-    if (!one_wave) {
+    if (FW > 1) {
       __syncthreads();
-      if (wv == 0)
-        st_partials(xp, nt, tile, s_red[0] + s_red[3] + s_red[6] + s_red[9],
-                    s_red[1] + s_red[4] + s_red[7] + s_red[10], s_red[2] + s_red[5] + s_red[8] + s_red[11], stamp);
-      __syncthreads();
-      if (t < 3 * kPw) s_red[t] = 0.0;  // entries that no wave writes below stay zero
-      __syncthreads();
+      const int p = wv / FW;
+      if (p < TP && wv == p * FW && wg * TP + p < nt) {
+        double v[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          v[j] = s_fin[3 * wv + j];
+#pragma unroll
+          for (int w = 1; w < FW; ++w) v[j] += s_fin[3 * (wv + w) + j];
+        }
+        st_partials(xp, nt, wg * TP + p, v[0], v[1], v[2], stamp);
+      }
     }
   }
-  if (polls <= 0) ok = false;  // no wait may succeed, also where the cap leaves none to make
+  if (fall_back) {
+    // a tile that gave up has every tile leave the solve as k_cg_start left it, and tile 0
+    // run the per-launch steps of all tiles one after another
+    __syncthreads();
+    if (t == 0) s_flag[1] = ok ? (int)cg_decide(dec, kCgGo) : 0;
+    __syncthreads();
+    if (s_flag[1] == (int)kCgSolo) {
+      if (wg == 0) cg_solo<T, R>(dpd, n_iter);
+      return;
+    }
+  } else if (polls <= 0) {
+    ok = false;  // no wait may succeed, also where the cap leaves none to make
+  }
 #pragma unroll
   for (int k = 0; k < NS; ++k)
     if (own[k] >= 0) x[ce[k]] = s_xo[own[k]];
-  if (tile == 0 && t == 0 && done_it >= 0) {
+  if (wg == 0 && t == 0 && done_it >= 0) {
     st->pcg_done = 1;
     st->pcg_iters = done_it;
   }
@@ -2720,6 +2810,20 @@ __global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, int n_iter) {
     st->pcg_fault = 1;
     st->pcg_done = 1;
   }
+}
+
+// The run of one problem, its descriptor passed by value, and of every problem of a batch
+// (the problems' tiles do not wait for one another).
+template <class T, int R, int NS, int TP>
+__global__ __launch_bounds__(1024) void k_cg_run(const ProbDev pd, const ProbDev *__restrict__ probs, int n_iter,
+                                                 int fall_back) {
+  cg_run_body<T, R, NS, TP>(pd, probs, (int)blockIdx.x, n_iter, fall_back != 0);
+}
+template <class T, int R, int NS>
+__global__ __launch_bounds__(1024) void k_cg_run_batch(const ProbDev *__restrict__ probs,
+                                                       const Tile *__restrict__ tiles, int n_iter) {
+  const Tile tl = tiles[blockIdx.x];
+  cg_run_body<T, R, NS, 1>(probs[tl.prob], probs + tl.prob, tl.idx, n_iter, true);
 }
 
 // The step kernels of one compute type for a launch whose problems all tile their rows
@@ -2742,17 +2846,32 @@ struct CgStep {
       default: return (const void *)k_cg_step1<T, 0>;
     }
   }
+  // the resident PCG for tiles of R rows whose longest column list is max_tcols, per_wg
+  // tiles to a workgroup (2: 16- and 32-row tiles of at most one column set)
   template <int NS>
   static const void *resident_sets(int R) {
     switch (R) {
-      case kPcgRows: return (const void *)k_cg_run<T, kPcgRows, NS>;
-      case kPcgRowsSparse: return (const void *)k_cg_run<T, kPcgRowsSparse, NS>;
-      default: return (const void *)k_cg_run<T, kPcgRowsMax, NS>;
+      case kPcgRows: return (const void *)k_cg_run<T, kPcgRows, NS, 1>;
+      case kPcgRowsSparse: return (const void *)k_cg_run<T, kPcgRowsSparse, NS, 1>;
+      default: return (const void *)k_cg_run<T, kPcgRowsMax, NS, 1>;
     }
   }
-  // the resident PCG for tiles of R rows whose longest column list is max_tcols
-  static const void *resident(int R, int max_tcols) {
+  static const void *resident(int R, int max_tcols, int per_wg) {
+    if (per_wg == 2)
+      return R == kPcgRowsSparse ? (const void *)k_cg_run<T, kPcgRowsSparse, 2, 2>
+                                 : (const void *)k_cg_run<T, kPcgRowsMax, 2, 2>;
     return max_tcols > kCgSetCols ? resident_sets<2>(R) : resident_sets<1>(R);
+  }
+  template <int NS>
+  static const void *batch_sets(int R) {
+    switch (R) {
+      case kPcgRows: return (const void *)k_cg_run_batch<T, kPcgRows, NS>;
+      case kPcgRowsSparse: return (const void *)k_cg_run_batch<T, kPcgRowsSparse, NS>;
+      default: return (const void *)k_cg_run_batch<T, kPcgRowsMax, NS>;
+    }
+  }
+  static const void *resident_batch(int R, int max_tcols) {
+    return max_tcols > kCgSetCols ? batch_sets<2>(R) : batch_sets<1>(R);
   }
 };
 
@@ -4118,8 +4237,9 @@ struct Timed {
 // LDS available to the fused PCG form for z (bytes): the device's per-workgroup
 // limit less room for the kernel's static LDS, set once by prepare_kernels().
 static size_t g_fused_lds = 48 * 1024;
-// Whether the resident PCG may use its LDS on this device.
+// Whether the resident PCG may use its LDS on this device, and the device's CUs.
 static bool g_run_ok = false;
+static int g_n_cu = 0;
 // Per-workgroup LDS of the device (0 when the chunk form cannot be used).
 static size_t g_lds_limit = 0;
 // Whether the dense form's product kernel may use its LDS on this device.
@@ -4146,17 +4266,27 @@ int prepare_kernels() {
     }
   }
   g_fused_lds = use;
-  // the resident PCG: the dynamic LDS of its longest column list
-  g_run_ok = true;
-  for (int R : {kPcgRows, kPcgRowsSparse, kPcgRowsMax})
-    for (int cols : {kCgSetCols, 2 * kCgSetCols})
-      for (int p = 0; p < 2; ++p)
-        if (hipFuncSetAttribute(p ? CgStep<float>::resident(R, cols) : CgStep<double>::resident(R, cols),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)cg_run_lds_bytes(cols, p ? 4 : 8)) != hipSuccess) {
-          (void)hipGetLastError();
-          g_run_ok = false;
-        }
+  // the resident PCG: the dynamic LDS of its longest column lists
+  g_run_ok = hipDeviceGetAttribute(&g_n_cu, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && g_n_cu > 0;
+  auto allow_run = [&](const void *f, int cols, size_t tbytes, int per_wg) {
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)cg_run_lds_bytes(cols, tbytes, per_wg)) != hipSuccess) {
+      (void)hipGetLastError();
+      g_run_ok = false;
+    }
+  };
+  for (int R : {kPcgRows, kPcgRowsSparse, kPcgRowsMax}) {
+    for (int cols : {kCgSetCols, 2 * kCgSetCols}) {
+      allow_run(CgStep<double>::resident(R, cols, 1), cols, 8, 1);
+      allow_run(CgStep<float>::resident(R, cols, 1), cols, 4, 1);
+      allow_run(CgStep<double>::resident_batch(R, cols), cols, 8, 1);
+      allow_run(CgStep<float>::resident_batch(R, cols), cols, 4, 1);
+    }
+    if (R != kPcgRows) {
+      allow_run(CgStep<double>::resident(R, kCgSetCols, 2), kCgSetCols, 8, 2);
+      allow_run(CgStep<float>::resident(R, kCgSetCols, 2), kCgSetCols, 4, 2);
+    }
+  }
   g_lds_limit = lim > 0 ? (size_t)lim : 0;
   // the chunk form stages a chunk in up to chunk_lds_bytes of dynamic LDS
   const void *chunk_kernels[4] = {(const void *)k_schur_chunk<double, double>,
@@ -4206,20 +4336,81 @@ bool one_reduction_pcg(int precision, int max_tcols) {
   return 6 * (size_t)max_tcols * (precision == 0 ? 8 : 4) <= g_fused_lds;
 }
 
-bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols) {
-  if (prepare_kernels() != 0 || !one_reduction_pcg(precision, max_tcols)) return false;
-  if (!g_run_ok || 6 * max_tcols > kCgColThreads || n_tiles < 1 || n_tiles > kCgRunTiles) return false;
-  const void *f =
-      precision == 0 ? CgStep<double>::resident(rows, max_tcols) : CgStep<float>::resident(rows, max_tcols);
-  const size_t lds = cg_run_lds_bytes(max_tcols, precision == 0 ? 8 : 4);
-  int dev = 0, n_cu = 0, per_cu = 0;
-  if (hipGetDevice(&dev) != hipSuccess ||
-      hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kCgThreads, lds) != hipSuccess) {
+// Whether a CU holds a workgroup of a resident kernel.
+static bool run_kernel_fits(const void *f, int max_tcols, size_t tbytes, int per_wg) {
+  int per_cu = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, f, kCgThreads,
+                                                   cg_run_lds_bytes(max_tcols, tbytes, per_wg)) != hipSuccess) {
     (void)hipGetLastError();
     return false;
   }
-  return per_cu >= 1 && n_tiles <= n_cu;
+  return per_cu >= 1;
+}
+
+bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols) {
+  if (prepare_kernels() != 0 || !one_reduction_pcg(precision, max_tcols)) return false;
+  if (!g_run_ok || 6 * max_tcols > kCgColThreads || n_tiles < 1 || n_tiles > std::min(g_n_cu, kCgRunTiles)) return false;
+  return run_kernel_fits(precision == 0 ? CgStep<double>::resident(rows, max_tcols, 1)
+                                        : CgStep<float>::resident(rows, max_tcols, 1),
+                         max_tcols, compute_bytes(precision), 1);
+}
+
+int device_cus() { return prepare_kernels() == 0 ? g_n_cu : 0; }
+
+int falling_back_pcg(int precision, int rows, int n_tiles, int max_tcols) {
+  if (prepare_kernels() != 0 || !one_reduction_pcg(precision, max_tcols)) return 0;
+  if (!g_run_ok || n_tiles < 1 || n_tiles > kCgRunTiles) return 0;
+  // one tile per workgroup while the CUs hold them, else two where a set holds a tile's columns
+  const int per_wg = n_tiles <= g_n_cu ? 1 : 2;
+  if (max_tcols > (per_wg == 1 ? 2 : 1) * kCgSetCols || (per_wg == 2 && rows == kPcgRows)) return 0;
+  const bool fits = run_kernel_fits(precision == 0 ? CgStep<double>::resident(rows, max_tcols, per_wg)
+                                                   : CgStep<float>::resident(rows, max_tcols, per_wg),
+                                    max_tcols, compute_bytes(precision), per_wg);
+  return fits ? per_wg : 0;
+}
+
+// The PCG of a plan after k_cg_start: one resident launch where the plan asks for it, else
+// one launch per iteration.
+template <class T>
+static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hipStream_t s, KernelTimer *tm) {
+  const bool flagged = bp.n_probs == 1 && bp.single.pcg_resident && bp.single.rig_mode == 0;
+  const int per_wg = flagged ? 1 : bp.pcg_run;
+  // one event pair around the whole run: per-launch events would add their own
+  // overhead to launches this short
+  Timed t(tm, K_PCG_CG, s, per_wg ? 1 : pcg_max);
+  hipError_t le = hipSuccess;
+  if (per_wg) {
+    const unsigned lds = (unsigned)cg_run_lds_bytes(max_tcols, sizeof(T), per_wg);
+    if (bp.n_probs > 1) {
+      void *args[] = {(void *)&bp.probs, (void *)&bp.pcg, (void *)&pcg_max};
+      return hipLaunchKernel(CgStep<T>::resident_batch(bp.pcg_rows, max_tcols), dim3(bp.n_pcg), dim3(kCgThreads), args,
+                             lds, s);
+    }
+    const void *f = CgStep<T>::resident(bp.pcg_rows, max_tcols, per_wg);
+    int fall_back = flagged ? 0 : 1;
+    void *args[] = {(void *)&bp.single, (void *)&bp.probs, (void *)&pcg_max, (void *)&fall_back};
+    const dim3 grid((bp.n_pcg + per_wg - 1) / per_wg);
+    // cooperative: the runtime places every workgroup at once or fails the launch;
+    // otherwise the occupancy count made at set-up stands, and in both cases the exchange's
+    // bounded wait turns starvation into a reported status
+    return flagged && bp.single.pcg_resident == 2 ? hipLaunchCooperativeKernel(f, grid, dim3(kCgThreads), args, lds, s)
+                                       : hipLaunchKernel(f, grid, dim3(kCgThreads), args, lds, s);
+  }
+  const size_t ubytes = 6 * (size_t)max_tcols * sizeof(T);
+  if (bp.n_probs == 1) {
+    const void *f = CgStep<T>::single(bp.pcg_rows);
+    for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
+      void *args[] = {(void *)&bp.single, (void *)&it};
+      le = hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, ubytes, s);
+    }
+  } else {
+    const void *f = CgStep<T>::multi(bp.pcg_rows);
+    for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
+      void *args[] = {(void *)&bp.probs, (void *)&bp.pcg, (void *)&it};
+      le = hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, ubytes, s);
+    }
+  }
+  return le;
 }
 
 template <class T, class S>
@@ -4297,34 +4488,7 @@ static hipError_t lm_iteration(const BatchPlan &bp, int pcg_max, int max_tcols, 
   }
   }
   if (pcg && bp.n_pcg && one_reduction) {
-    // one event pair around the whole run: per-launch events would add their own
-    // overhead to launches this short
-    const bool resident = bp.n_probs == 1 && bp.single.pcg_resident;
-    Timed t(tm, K_PCG_CG, s, resident ? 1 : pcg_max);
-    hipError_t le = hipSuccess;
-    if (resident) {
-      const void *f = CgStep<T>::resident(bp.pcg_rows, max_tcols);
-      void *args[] = {(void *)&bp.single, (void *)&pcg_max};
-      const unsigned lds = (unsigned)cg_run_lds_bytes(max_tcols, sizeof(T));
-      // cooperative: the runtime places every workgroup at once or fails the launch;
-      // otherwise the occupancy count made at set-up stands, and in both cases the grid
-      // barrier's bounded wait turns starvation into a reported status
-      le = bp.single.pcg_resident == 2
-               ? hipLaunchCooperativeKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, lds, s)
-               : hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, lds, s);
-    } else if (bp.n_probs == 1) {
-      const void *f = CgStep<T>::single(bp.pcg_rows);
-      for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
-        void *args[] = {(void *)&bp.single, (void *)&it};
-        le = hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, ubytes, s);
-      }
-    } else {
-      const void *f = CgStep<T>::multi(bp.pcg_rows);
-      for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
-        void *args[] = {(void *)&bp.probs, (void *)&bp.pcg, (void *)&it};
-        le = hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, ubytes, s);
-      }
-    }
+    const hipError_t le = launch_pcg<T>(bp, pcg_max, max_tcols, s, tm);
     if (le != hipSuccess) return le;
   } else if (pcg) {
     for (int it = 0; it < pcg_max && bp.n_pcg; ++it) {
@@ -4432,21 +4596,7 @@ static hipError_t rig_iteration(const BatchPlan &cp, const BatchPlan &rp, int pc
       else
         k_cg_start<T, 4><<<rp.n_pcg, 256, 0, s>>>(rp.probs, rp.pcg);
     }
-    Timed t(tm, K_PCG_CG, s, pcg_max);
-    hipError_t le = hipSuccess;
-    if (rp.n_probs == 1) {  // the rig view's descriptor by value
-      const void *f = CgStep<T>::single(rp.pcg_rows);
-      for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
-        void *args[] = {(void *)&rp.single, (void *)&it};
-        le = hipLaunchKernel(f, dim3(rp.n_pcg), dim3(kCgThreads), args, ubytes, s);
-      }
-    } else {
-      const void *f = CgStep<T>::multi(rp.pcg_rows);
-      for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
-        void *args[] = {(void *)&rp.probs, (void *)&rp.pcg, (void *)&it};
-        le = hipLaunchKernel(f, dim3(rp.n_pcg), dim3(kCgThreads), args, ubytes, s);
-      }
-    }
+    const hipError_t le = launch_pcg<T>(rp, pcg_max, max_tcols, s, tm);
     if (le != hipSuccess) return le;
   } else {
     for (int it = 0; it < pcg_max && rp.n_pcg; ++it) {

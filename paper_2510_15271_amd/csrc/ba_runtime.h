@@ -68,6 +68,7 @@ struct Symbolic {
   int32_t max_tcols = 0;
   int32_t pcg_rows = kPcgRows;    // rows per PCG tile
   bool pcg_resident = false;      // the whole PCG in one launch (BA_FLAG_PCG_RESIDENT, when it fits)
+  int pcg_run = 0;                // tiles per workgroup of the falling-back one-launch PCG, 0: does not fit
   bool pcg_coop = false;          // ... started as a cooperative launch (BA_FLAG_PCG_COOPERATIVE)
 };
 // Edges of a pose graph: node pairs (i, j), measured A_ij (12 values each, R row-major
@@ -91,7 +92,7 @@ struct Offsets {
   size_t pp_cam, pp_meas, pp_w, pp_up, cam_pp_start, cam_pp, prior_diag, prior_off;
   size_t pose[2], X[2], pose_init, X_init, lin, Q, V, gp, Dp, Vinv, gc, Dc, brhs, S, Minv, vec[14];
   size_t part_lin_cost, part_masked, part_sq, part_trial_cost, part_trial_masked, part_dl_pt, part_dl_cam;
-  size_t part_rz0, part_bb, part_rz[2], part_pq, part_rr, part_cg[2], cg_xw[2], cg_xp[2], part_prior, part_cull, iter_cost, iter_pcg;
+  size_t part_rz0, part_bb, part_rz[2], part_pq, part_rr, part_cg[2], cg_xw[2], cg_xp[2], cg_dec, part_prior, part_cull, iter_cost, iter_pcg;
   size_t total;
 };
 
@@ -184,6 +185,14 @@ struct PoseBatch {
   // Upload, launch and queue the download of the headers into hdr (caller syncs).
   int run(char *base, hipStream_t s, KernelTimer *tm);
 };
+// A count of the CUs that one-launch PCG runs may occupy at once on a device, so that the
+// workgroups of two of them never wait for each other's CUs: a solve (or a server) takes
+// the CUs of its run before it queues it and gives them back when the run has ended, or
+// launches its PCG per iteration when they are not free.  take_cus counts n in any case if
+// `always` (a run the caller has asked for by flag).  Thread-safe.
+bool take_cus(int device, int n, bool always);
+void give_cus(int device, int n);
+
 int check_pose_request(const ba_pose_request &r, int64_t i);
 
 }  // namespace bax

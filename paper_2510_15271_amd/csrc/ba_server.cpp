@@ -197,6 +197,8 @@ struct ba_server {
   std::thread th, up_th;
   std::vector<std::thread> ana_th;
   Batch batch, fin_batch;
+  int device = 0;
+  int cus = 0;  // CUs taken for one-launch PCG runs, while there is work in flight
   hipEvent_t ev_step[kLookahead] = {};
   int64_t n_steps = 0;
   std::vector<Pinned> pinned_free;
@@ -212,6 +214,7 @@ struct ba_server {
   void finish(const std::vector<ReqP> &done_now);
   Pinned take_pinned(size_t n);
   int complete(bool block);
+  int batch_run(int max_tcols);
   bool idle_locked() const {
     return ana_q.empty() && analysing == 0 && ready.empty() && pose_q.empty() && up_q.empty() &&
            uploading == 0 && uploaded.empty() && active.empty() && completing.empty();
@@ -359,6 +362,21 @@ int ba_server::complete(bool block) {
   return BA_OK;
 }
 
+// Whether the batch's linear solves run in one launch: every problem's tiles at once, one
+// workgroup each, where the device holds them beside the other such runs in flight.  The
+// CUs stay taken until the server is idle (earlier launches may still be running).
+int ba_server::batch_run(int max_tcols) {
+  const int rows = batch.plan.pcg_rows, n = batch.plan.n_pcg;
+  if (rows == 0 || n > device_cus()) return 0;
+  for (const ProbDev &pd : batch.probs)
+    if (falling_back_pcg(precision, rows, pd.n_pcg_tiles, max_tcols) != 1) return 0;
+  if (n > cus) {
+    if (!take_cus(device, n - cus, false)) return 0;
+    cus = n;
+  }
+  return 1;
+}
+
 void ba_server::loop() {
   bool dirty = true;
   while (true) {
@@ -414,6 +432,7 @@ void ba_server::loop() {
       }
     }
     if (!active.empty() && fatal == BA_OK) {
+      const bool joined = dirty;
       if (dirty) {
         batch.clear();
         for (size_t i = 0; i < active.size(); ++i) batch.add(active[i]->dp.view, (int)i);
@@ -425,6 +444,7 @@ void ba_server::loop() {
         pcg_max = std::max(pcg_max, r->dp.pcg_max);
         max_cf = std::max(max_cf, (int)r->dp.max_tcols);
       }
+      if (joined && fatal == BA_OK) batch.plan.pcg_run = batch_run(max_cf);
       // at most kLookahead launch sequences in flight
       hipEvent_t &ev = ev_step[n_steps % kLookahead];
       if (fatal == BA_OK && n_steps >= kLookahead && hipEventSynchronize(ev) != hipSuccess) fatal = BA_EDEVICE;
@@ -496,10 +516,16 @@ void ba_server::loop() {
     if (fatal == BA_OK) {
       const bool nothing_launched = pose_now.empty() && active.empty();
       if (complete(nothing_launched) != BA_OK) fatal = BA_EDEVICE;
+      if (cus && active.empty() && completing.empty()) {  // every launch's results have landed
+        give_cus(device, cus);
+        cus = 0;
+      }
     }
     if (fatal != BA_OK) {
       // fail everything still pending; the device state is unknown
       (void)hipStreamSynchronize(stream);
+      if (cus) give_cus(device, cus);
+      cus = 0;
       std::vector<ReqP> all;
       {
         std::lock_guard<std::mutex> lk(mu);
@@ -539,6 +565,7 @@ int ba_server_create(int64_t hbm_budget_bytes, int32_t max_slots, int32_t precis
   if (precision < BA_PREC_F64 || precision > BA_PREC_BF16J) return fail(BA_EINVAL, "unknown precision");
   if (prepare_kernels() != 0) return fail(BA_EDEVICE, "no HIP device");
   std::unique_ptr<ba_server> s(new ba_server());
+  (void)hipGetDevice(&s->device);
   s->budget = hbm_budget_bytes;
   s->max_slots = max_slots;
   s->precision = precision;

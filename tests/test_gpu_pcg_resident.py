@@ -7,7 +7,7 @@ import numpy as np
 import pytest
 
 from oracle import ba_oracle as O
-from synth import make_arc_scene, make_config1, make_pose_graph, make_small_drive
+from synth import make_arc_scene, make_config1, make_pose_graph, make_rig_drive, make_small_drive
 
 pytestmark = pytest.mark.gpu
 
@@ -190,3 +190,58 @@ def test_resident_exchange_edges(balib, prec, case):
     _say("rows", ib["pcg_rows"], "resident", ib["pcg_resident"], "pcg", list(b["pcg_iters"]))
     assert ib["pcg_resident"] == 1 and ib["pcg_rows"] == 4
     _same(a, b)
+
+
+def _one_launch_problem(balib, case, prec):
+    kw = dict(max_iters=3, pcg_max_iters=30, pcg_rel_tol=1e-10, precision=prec)
+    if case == "graph pairs":  # 282 tiles of 32 rows, two to a workgroup
+        return balib.Problem.from_pose_graph(make_pose_graph(1500), **kw)
+    if case == "graph 16 rows":
+        return balib.Problem.from_pose_graph(make_pose_graph(180), **kw)
+    if case == "rig":
+        return balib.Problem.from_rig(make_rig_drive(40, 1500, seed=3), prior_ext=100.0, prior_rig=100.0,
+                                      rig_pairs=np.array([[0, 1], [0, 2]]), **kw)
+    s = {"small": lambda: make_small_drive(40, 3000, seed=5),
+         "one tile": lambda: make_arc_scene(5, 300, seed=4),
+         "columns": lambda: make_arc_scene(168, 1200, seed=9),
+         "16 rows, columns": lambda: make_small_drive(1100, 22000, seed=9, mean_track=16.0)}[case]()
+    return balib.Problem.from_scene(s, **kw)
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("case", ["one tile", "small", "columns", "16 rows, columns", "graph 16 rows", "graph pairs",
+                                  "rig"])
+def test_one_launch_pcg_equals_one_workgroup(balib, prec, case):
+    """Without a flag the PCG runs in one launch that falls back to one workgroup, which
+    runs the launch-per-iteration steps of every tile in turn, when its tiles are not all
+    running; the poll bound set to 0 makes it fall back in every linear solve.  Both give
+    the same solve bit for bit, and an ordinary status."""
+    _say("device solves:", case, prec)
+    p = _one_launch_problem(balib, case, prec)
+    info = p.info()
+    assert info["pcg_resident"] == 0
+    a = p.solve().result()
+    p.set_barrier_polls(0)
+    b = p.reset().solve().result()
+    p.close()
+    _say("rows", info["pcg_rows"], "pcg", list(a["pcg_iters"]), list(b["pcg_iters"]), "status", a["status"], b["status"])
+    assert a["status"] in (0, 1) and a["iters"] == 3
+    _same(a, b)
+
+
+def test_one_launch_pcg_beside_another(balib):
+    """Two solves in flight at once whose tiles (175 each) do not fit the device together:
+    the second launches its PCG per iteration.  Both equal the solves made alone."""
+    s = make_small_drive(700, 14000, seed=8)
+    kw = dict(max_iters=4, pcg_max_iters=40, pcg_rel_tol=1e-10, precision="f32")
+    _, alone = _run(balib, s, 0, **kw)
+    ps = [balib.Problem.from_scene(s, **kw) for _ in range(2)]
+    for _ in range(2):
+        for p in ps:
+            p.reset().solve_async()
+        for p in ps:
+            p.wait()
+        for p in ps:
+            _same(alone, p.result())
+    for p in ps:
+        p.close()
