@@ -265,3 +265,23 @@ def test_ransac_triangulation_full_size_sampled(balib):
     _say("ok", int(ok.sum()), "outliers flagged", float((~inl & s.outlier).sum() / s.outlier.sum()),
          "inliers kept", float((inl & ~s.outlier).sum() / (~s.outlier).sum()), "max rel err", worst, "device ms", ms)
     assert worst <= 1e-8
+
+
+@pytest.mark.parametrize("n_hyp", [1, 8, 9, 17, 33, 65, 130])
+def test_ransac_lane_groups(balib, n_hyp):
+    """Hypothesis counts around the lanes per track (8, 16, 32, 64) and past one round of
+    them, on tracks of 1 to about 100 observations (longer than a group) with 10 %
+    outliers: the outcomes and every inlier flag equal the oracle's and the points agree
+    within 1e-7 relative (FP64 rounding times the conditioning of short-baseline tracks, as above)."""
+    s = make_small_drive(120, 90, seed=73, outlier_frac=0.1, mean_track=45.0)
+    p = O.Problem.from_scene(s)
+    p.R, p.t = O.quat_to_rot(s.q_gt), np.array(s.t_gt)
+    d = balib.scene_desc(s)
+    d.poses[:, :4], d.poses[:, 4:] = s.q_gt, s.t_gt
+    _say("device ransac triangulation:", n_hyp, "hypotheses, longest track", int(np.bincount(s.obs_pt).max()))
+    X, ok, inl, _ = balib.triangulate_ransac(d, 3.0, n_hyp, "midpoint")
+    for j in range(s.n_pts):
+        Xo, oko, ino = O.triangulate_ransac(p, j, 3.0, n_hyp, "midpoint")
+        assert bool(ok[j]) == bool(oko) and np.array_equal(inl[p.pt == j], ino), j
+        if oko:
+            assert np.linalg.norm(X[j] - Xo) <= 1e-7 * (1 + np.linalg.norm(Xo)), j
