@@ -716,6 +716,7 @@ int analyse(const ba_problem_desc *d, const ba_options *opt, Symbolic &sy, const
   sy.pcg_resident = (opt->flags & BA_FLAG_PCG_RESIDENT) &&
                     resident_pcg_fits(prec, sy.pcg_rows, (Cf + sy.pcg_rows - 1) / sy.pcg_rows, sy.max_tcols);
   sy.pcg_coop = sy.pcg_resident && (opt->flags & BA_FLAG_PCG_COOPERATIVE);
+  sy.pcg_small = one_workgroup_pcg(prec, sy.pcg_rows, Cf);
   sy.pcg_run = falling_back_pcg(prec, sy.pcg_rows, (Cf + sy.pcg_rows - 1) / sy.pcg_rows, sy.max_tcols);
   if (sy.dense) {
     // first record of each point in each camera tile: the point's records in the tile
@@ -954,6 +955,7 @@ int DevProblem::init(const Symbolic &sy, const ba_problem_desc *d, const ba_opti
   pd.pt_tile = sy.pt_tile;
   pd.n_pcg_tiles = (Cf + sy.pcg_rows - 1) / sy.pcg_rows;
   pd.pcg_rows = sy.pcg_rows;
+  pd.pcg_small = sy.pcg_small ? 1 : 0;
   pd.pcg_resident = sy.pcg_resident ? (sy.pcg_coop ? 2 : 1) : 0;
   pd.n_cam_tiles = (C + kCamTile - 1) / kCamTile;
   pd.K = ptr(off.K);
@@ -1201,6 +1203,9 @@ void Batch::add(const ProbDev &pd, int slot_tag) {
     for (int t = 0; t < (pd.n_up + kOffWaves - 1) / kOffWaves; ++t) tiles[2].push_back(Tile{pi, t});
   }
   for (int t = 0; t < pd.n_pcg_tiles; ++t) tiles[3].push_back(Tile{pi, t});
+  if (pd.pcg_small) tiles[16].push_back(Tile{pi, 0});
+  else
+    for (int t = 0; t < pd.n_pcg_tiles; ++t) tiles[17].push_back(Tile{pi, t});
   for (int t = 0; t < pd.n_cam_tiles; ++t) tiles[4].push_back(Tile{pi, t});
   tiles[5].push_back(Tile{pi, 0});
   for (int t = 0; t < pd.n_pri_tiles; ++t) tiles[11].push_back(Tile{pi, t});
@@ -1226,7 +1231,7 @@ int Batch::upload(hipStream_t s) {
   xcd_contiguous(tiles[2]);
   xcd_contiguous(tiles[7]);
   size_t need = probs.size() * sizeof(ProbDev);
-  constexpr int NL = 16;
+  constexpr int NL = 18;
   size_t offs[NL];
   for (int i = 0; i < NL; ++i) {
     need = (need + 255) & ~size_t(255);
@@ -1251,18 +1256,21 @@ int Batch::upload(hipStream_t s) {
   plan.probs = (const ProbDev *)b;
   const Tile **dst[NL] = {&plan.pt, &plan.diag, &plan.off, &plan.pcg, &plan.cam, &plan.ctl,
                           &plan.pp, &plan.ch, &plan.red, &plan.fin, &plan.fsh, &plan.pri,
-                          &plan.dpt, &plan.dcm, &plan.dsy, &plan.dre};
+                          &plan.dpt, &plan.dcm, &plan.dsy, &plan.dre, &plan.pcs, &plan.pcb};
   int32_t *cnt[NL] = {&plan.n_pt, &plan.n_diag, &plan.n_off, &plan.n_pcg, &plan.n_cam, &plan.n_ctl,
                       &plan.n_pp, &plan.n_ch, &plan.n_red, &plan.n_fin, &plan.n_fsh, &plan.n_pri,
-                      &plan.n_dpt, &plan.n_dcm, &plan.n_dsy, &plan.n_dre};
+                      &plan.n_dpt, &plan.n_dcm, &plan.n_dsy, &plan.n_dre, &plan.n_pcs, &plan.n_pcb};
   for (int i = 0; i < NL; ++i) {
     *dst[i] = (const Tile *)(b + offs[i]);
     *cnt[i] = (int32_t)tiles[i].size();
   }
   plan.n_probs = (int32_t)probs.size();
   plan.pcg_rows = probs.empty() ? kPcgRows : probs[0].pcg_rows;
-  for (const ProbDev &pd : probs)
+  plan.big_rows = -1;
+  for (const ProbDev &pd : probs) {
     if (pd.pcg_rows != plan.pcg_rows) plan.pcg_rows = 0;
+    if (!pd.pcg_small) plan.big_rows = plan.big_rows < 0 || plan.big_rows == pd.pcg_rows ? pd.pcg_rows : 0;
+  }
   if (probs.size() == 1) plan.single = probs[0];
   return BA_OK;
 }
@@ -1981,13 +1989,14 @@ int ba_solve_async(ba_problem *p) {
   const Symbolic &sy = p->rig ? p->rig->sy : p->sy;
   const bool flagged = !p->rig && sy.pcg_resident;
   const int per_wg = flagged ? 1 : sy.pcg_run;
-  const int n = per_wg ? ((sy.Cf + sy.pcg_rows - 1) / sy.pcg_rows + per_wg - 1) / per_wg : 0;
-  const bool one = n > 0 && take_cus(p->device, n, flagged);
+  // (one workgroup waits for no other)
+  const int n = per_wg && !sy.pcg_small ? ((sy.Cf + sy.pcg_rows - 1) / sy.pcg_rows + per_wg - 1) / per_wg : 0;
+  const bool one = sy.pcg_small || (n > 0 && take_cus(p->device, n, flagged));
   if (one) p->cus = n;
   (p->rig ? p->rig->batch : p->batch).plan.pcg_run = one ? per_wg : 0;
   const int rc = queue_solve(p, one);
   if (rc != BA_OK) {
-    if (one) (void)hipStreamSynchronize(p->stream);  // whatever was queued before the error
+    if (p->cus) (void)hipStreamSynchronize(p->stream);  // whatever was queued before the error
     p->give_back_cus();
   }
   return rc;

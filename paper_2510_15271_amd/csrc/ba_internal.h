@@ -98,6 +98,7 @@ struct ProbDev {
   int32_t max_tcols;     // longest tile column list
   int32_t pcg_rows;      // rows per PCG tile: kPcgRows, kPcgRowsSparse or kPcgRowsMax
   int32_t pcg_resident;  // 1: the whole PCG runs in one launch with grid barriers (k_cg_run); 2: launched cooperatively
+  int32_t pcg_small;     // 1: the whole PCG by one workgroup (k_cg_small)
   int32_t chunked;       // 1: point-chunk Schur form, 0: pair-list form
   int32_t n_ch;          // point chunks (chunk form)
   int32_t n_red_tiles;   // reduction tiles (chunk form): four upper blocks each
@@ -241,8 +242,12 @@ struct BatchPlan {
   // workgroups (Z Z^T) and tile pairs (reduction)
   const Tile *dpt, *dcm, *dsy, *dre;
   int32_t n_dpt, n_dcm, n_dsy, n_dre;
+  // the problems whose PCG one workgroup runs, and the PCG tiles of the others
+  const Tile *pcs, *pcb;
+  int32_t n_pcs, n_pcb;
   int32_t n_probs;
   int32_t pcg_rows;  // rows per PCG tile shared by every problem of the batch, 0 if mixed
+  int32_t big_rows;  // ... by those whose PCG takes more than one workgroup
   int32_t pcg_run;   // the PCG in one launch that falls back to one workgroup when its tiles
                      // cannot all run at once: tiles per workgroup, 0: a launch per iteration
   ProbDev single;  // host copy of the descriptor when n_probs == 1 (passed by value to short kernels)
@@ -297,6 +302,8 @@ bool one_reduction_pcg(int precision, int max_tcols);
 // True when the resident PCG (one launch, grid barriers) can run a problem: every
 // tile's columns fit one sweep and all n_tiles workgroups can be resident at once.
 bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols);
+// Whether one workgroup runs the PCG of a problem of Cf free cameras in 4-row tiles.
+bool one_workgroup_pcg(int precision, int rows, int Cf);
 // CUs of the current device (0: none present).
 int device_cus();
 // Tiles per workgroup (1 or 2) of the PCG in one launch that falls back (BatchPlan::pcg_run)

@@ -2826,6 +2826,204 @@ __global__ __launch_bounds__(1024) void k_cg_run_batch(const ProbDev *__restrict
   cg_run_body<T, R, NS, 1>(probs[tl.prob], probs + tl.prob, tl.idx, n_iter, true);
 }
 
+// The one-reduction PCG of a problem of few cameras by one workgroup: nothing is exchanged
+// between workgroups, so an iteration is four barriers.  The same iterates, bit for bit:
+// element (row a, component m) belongs to one thread, which keeps its r, s, p and x and
+// advances them; the products S u follow the per-launch step's 4-row layout (a row's
+// blocks in runs of ten, six lanes each, the runs' sums in order), one (row, run) at a
+// time per wave with the S blocks in registers, the lanes' sums left in LDS for the
+// element's thread to add; and wave 0 forms the 4-row tiles' partial sums and their total
+// in the order of wave_sum (a tile's 24 elements, then the tiles, in the 16-lane rows that
+// the butterfly's first two steps leave).  Against the tiles' exchange an iteration of 20
+// cameras in FP32 went from 3.3 to 2.1 us, of 8 in FP64 from 4.4 to 1.9 (both with the
+// launch, over some 50 and 16 iterations).
+constexpr int kCgSmallTasks = 10;  // (row, run) products per wave, at most (FP64: 5)
+template <class T>
+constexpr int cg_small_cams() { return sizeof(T) == 4 ? 40 : 24; }
+
+// v summed over the 16 lanes of a row as wave_sum does after its first two steps
+__device__ __forceinline__ double row_sum(double v) {
+  v = lane_pair_sum<8>(v);
+  v = lane_pair_sum<4>(v);
+  v = lane_pair_sum<2>(v);
+  return lane_pair_sum<1>(v);
+}
+
+template <class T>
+__device__ __forceinline__ void cg_small_body(const ProbDev &pd, const ProbDev *dpd, int n_iter,
+                                              const bool fall_back) {
+  constexpr int kC = cg_small_cams<T>(), kQ = (kC + 9) / 10, kTask = sizeof(T) == 4 ? kCgSmallTasks : 5;
+  static_assert(kC * kQ <= 16 * kTask && 6 * kC <= 256, "tasks of 16 waves, elements of the first waves");
+  __shared__ T s_u[6 * kC];
+  __shared__ T s_acc[kC * kQ][60];
+  __shared__ double s_dot[3][24 * 16];  // r.u, w.u, r.r terms, 24 per tile
+  __shared__ double s_pd[3][16];        // the tiles' partials
+  __shared__ double s_red[3];
+  __shared__ int s_flag[1];
+  LMState *st = pd.st;
+  const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int Cf = pd.Cf, nt = pd.n_pcg_tiles;
+  if (t == 0) s_flag[0] = (lm_active(st) && !st->pcg_done) ? 1 : 0;
+  __syncthreads();
+  if (!s_flag[0]) return;
+  n_iter = min(n_iter, st->pcg_max);
+  if (st->bar_polls <= 0) {  // the test hook: as a run whose workgroups do not meet
+    if (fall_back) {
+      cg_solo<T, kPcgRows>(dpd, n_iter);
+    } else if (t == 0) {
+      st->pcg_fault = 1;
+      st->pcg_done = 1;
+    }
+    return;
+  }
+  const double tol = st->pcg_tol, bb = st->pcg_bb;
+  // ---- the thread's element: ten columns to a wave
+  const bool col_lane = lane < 60;
+  const int cg = col_lane ? lane / 6 : 9, m = col_lane ? lane - 6 * cg : 0, c = 10 * wv + cg;
+  const bool has = col_lane && c < Cf;
+  const uint32_t e = has ? 6 * (uint32_t)c + (uint32_t)m : 0u;
+  const auto x = as_global((T *)pd.x);
+  T wc = as_global((const T *)pd.cg_w[0])[e], rc = as_global((const T *)pd.cg_r[0])[e], sc = T(0), pc = T(0);
+  T uc = as_global((const T *)pd.cg_u[0])[e], xc = x[e];
+  double mr[6];
+#pragma unroll
+  for (int n = 0; n < 6; ++n) mr[n] = as_global((const double *)pd.Minv)[6 * (size_t)e + n];
+  // ---- the wave's (row, run) products
+  const auto S = as_global((const T *)pd.S);
+  const int nq = (Cf + 9) / 10, n_task = Cf * nq;
+  T sreg[kTask][6];
+  int lreg[kTask];
+  const int i = col_lane ? m : 0;
+#pragma unroll
+  for (int k = 0; k < kTask; ++k) {
+    const int task = wv + 16 * k;
+    lreg[k] = -1;
+    if (task < n_task) {
+      const int a = task / nq, blk = as_global(pd.S_rowptr)[a] + 10 * (task - nq * a) + cg;
+      if (col_lane && blk < as_global(pd.S_rowptr)[a + 1]) {
+        lreg[k] = 6 * as_global(pd.S_col)[blk];
+#pragma unroll
+        for (int n = 0; n < 6; ++n) sreg[k][n] = S[36 * (size_t)blk + 6 * i + n];
+      } else if (col_lane) {
+        s_acc[task][lane] = T(0);
+      }
+    }
+  }
+  if (t < 48) s_pd[t / 16][t % 16] = t % 16 < nt ? as_global((const double *)pd.part_cg[0])[nt * (t / 16) + t % 16] : 0.0;
+  for (int k = t; k < 3 * 24 * 16; k += kCgThreads) (&s_dot[0][0])[k] = 0.0;  // ragged last tile
+  __syncthreads();
+  auto totals = [&]() {  // wave 0: the tiles' partials to their sums
+    const double v0 = row_sum(s_pd[0][lane & 15]), v1 = row_sum(s_pd[1][lane & 15]), v2 = row_sum(s_pd[2][lane & 15]);
+    if (lane == 0) {
+      s_red[0] = v0;
+      s_red[1] = v1;
+      s_red[2] = v2;
+    }
+  };
+  if (wv == 0) totals();
+  double gprev = 1.0, aprev = 1.0;
+  int done_it = -1;
+  for (int it = 0; it < n_iter; ++it) {
+    __syncthreads();
+    const double gam = s_red[0], del = s_red[1], rr = s_red[2];
+    if (it > 0 && sqrt(rr) <= tol * sqrt(bb)) {
+      done_it = it;
+      break;
+    }
+    double beta = 0.0, den = del;
+    if (it > 0) {
+      beta = gam / gprev;
+      den = del - beta * gam / aprev;
+    }
+    if (!(den > 0.0)) {
+      done_it = it + 1;
+      break;
+    }
+    const double alpha = gam / den;
+    gprev = gam;
+    aprev = alpha;
+    const T ta = T(alpha), tb = T(beta);
+    if (10 * wv < Cf) {
+      sc = wc + tb * sc;
+      rc = rc - ta * sc;
+      const int ca = 4 * (lane - m);
+      const T rn[6] = {lane_read<0>(ca, rc), lane_read<1>(ca, rc), lane_read<2>(ca, rc),
+                       lane_read<3>(ca, rc), lane_read<4>(ca, rc), lane_read<5>(ca, rc)};
+      double z = 0.0;
+#pragma unroll
+      for (int n = 0; n < 6; ++n) z += mr[n] * (double)rn[n];
+      const T un = T(z);
+      const T pn = uc + tb * pc;
+      pc = pn;
+      xc = xc + ta * pn;
+      uc = un;
+      if (has) s_u[e] = un;
+    }
+    if (it + 1 == n_iter) break;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < kTask; ++k)
+      if (lreg[k] >= 0) {
+        T acc = T(0);
+        const T *ul = s_u + lreg[k];
+#pragma unroll
+        for (int n = 0; n < 6; ++n) acc += sreg[k][n] * ul[n];
+        s_acc[wv + 16 * k][lane] = acc;
+      }
+    __syncthreads();
+    if (has) {
+      T w = T(0);
+      for (int q = 0; q < nq; ++q) {
+        T wi = T(0);
+#pragma unroll
+        for (int g = 0; g < 10; ++g) wi += s_acc[nq * c + q][6 * g + m];
+        w = q == 0 ? wi : w + wi;
+      }
+      wc = w;
+      const double ui = (double)uc, ri = (double)rc;
+      s_dot[0][e] = ri * ui;
+      s_dot[1][e] = (double)w * ui;
+      s_dot[2][e] = ri * ri;
+    }
+    __syncthreads();
+    if (wv == 0) {
+      const int l = lane & 15;
+      for (int k0 = 0; k0 < nt; k0 += 4) {  // four tiles at a time, one per row of lanes
+        const int k = k0 + (lane >> 4);
+        double v[3];
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const double *d = &s_dot[j][24 * k];
+          v[j] = l < 8 ? d[l] + d[16 + l] : d[l];
+          v[j] = row_sum(v[j]);
+        }
+        if (l == 0 && k < nt) {
+#pragma unroll
+          for (int j = 0; j < 3; ++j) s_pd[j][k] = v[j];
+        }
+      }
+      totals();
+    }
+  }
+  if (has) x[e] = xc;
+  if (t == 0 && done_it >= 0) {
+    st->pcg_done = 1;
+    st->pcg_iters = done_it;
+  }
+}
+
+template <class T>
+__global__ __launch_bounds__(1024) void k_cg_small(const ProbDev pd, const ProbDev *__restrict__ probs, int n_iter,
+                                                   int fall_back) {
+  cg_small_body<T>(pd, probs, n_iter, fall_back != 0);
+}
+template <class T>
+__global__ __launch_bounds__(1024) void k_cg_small_batch(const ProbDev *__restrict__ probs,
+                                                         const Tile *__restrict__ tiles, int n_iter) {
+  const int p = tiles[blockIdx.x].prob;
+  cg_small_body<T>(probs[p], probs + p, n_iter, true);
+}
+
 // The step kernels of one compute type for a launch whose problems all tile their rows
 // by R (0: mixed, read per problem).
 template <class T>
@@ -4355,6 +4553,10 @@ bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols) {
                          max_tcols, compute_bytes(precision), 1);
 }
 
+bool one_workgroup_pcg(int precision, int rows, int Cf) {
+  return rows == kPcgRows && Cf <= (precision == 0 ? cg_small_cams<double>() : cg_small_cams<float>());
+}
+
 int device_cus() { return prepare_kernels() == 0 ? g_n_cu : 0; }
 
 int falling_back_pcg(int precision, int rows, int n_tiles, int max_tcols) {
@@ -4373,42 +4575,45 @@ int falling_back_pcg(int precision, int rows, int n_tiles, int max_tcols) {
 // one launch per iteration.
 template <class T>
 static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hipStream_t s, KernelTimer *tm) {
-  const bool flagged = bp.n_probs == 1 && bp.single.pcg_resident && bp.single.rig_mode == 0;
+  const bool lone = bp.n_probs == 1, flagged = lone && bp.single.pcg_resident && bp.single.rig_mode == 0;
   const int per_wg = flagged ? 1 : bp.pcg_run;
+  int fall_back = flagged ? 0 : 1;
   // one event pair around the whole run: per-launch events would add their own
   // overhead to launches this short
-  Timed t(tm, K_PCG_CG, s, per_wg ? 1 : pcg_max);
+  Timed t(tm, K_PCG_CG, s, per_wg || bp.n_pcb == 0 ? 1 : pcg_max);
+  if (bp.n_pcs) {  // the problems that one workgroup solves
+    void *args1[] = {(void *)&bp.single, (void *)&bp.probs, (void *)&pcg_max, (void *)&fall_back};
+    void *argsn[] = {(void *)&bp.probs, (void *)&bp.pcs, (void *)&pcg_max};
+    const unsigned lds = 6 * cg_small_cams<T>() * sizeof(T);  // for cg_solo
+    const hipError_t le =
+        lone ? hipLaunchKernel((const void *)k_cg_small<T>, dim3(1), dim3(kCgThreads), args1, lds, s)
+             : hipLaunchKernel((const void *)k_cg_small_batch<T>, dim3(bp.n_pcs), dim3(kCgThreads), argsn, lds, s);
+    if (le != hipSuccess) return le;
+  }
+  if (bp.n_pcb == 0) return hipSuccess;
   hipError_t le = hipSuccess;
   if (per_wg) {
     const unsigned lds = (unsigned)cg_run_lds_bytes(max_tcols, sizeof(T), per_wg);
-    if (bp.n_probs > 1) {
-      void *args[] = {(void *)&bp.probs, (void *)&bp.pcg, (void *)&pcg_max};
-      return hipLaunchKernel(CgStep<T>::resident_batch(bp.pcg_rows, max_tcols), dim3(bp.n_pcg), dim3(kCgThreads), args,
+    if (!lone) {
+      void *args[] = {(void *)&bp.probs, (void *)&bp.pcb, (void *)&pcg_max};
+      return hipLaunchKernel(CgStep<T>::resident_batch(bp.big_rows, max_tcols), dim3(bp.n_pcb), dim3(kCgThreads), args,
                              lds, s);
     }
-    const void *f = CgStep<T>::resident(bp.pcg_rows, max_tcols, per_wg);
-    int fall_back = flagged ? 0 : 1;
+    const void *f = CgStep<T>::resident(bp.big_rows, max_tcols, per_wg);
     void *args[] = {(void *)&bp.single, (void *)&bp.probs, (void *)&pcg_max, (void *)&fall_back};
-    const dim3 grid((bp.n_pcg + per_wg - 1) / per_wg);
+    const dim3 grid((bp.n_pcb + per_wg - 1) / per_wg);
     // cooperative: the runtime places every workgroup at once or fails the launch;
     // otherwise the occupancy count made at set-up stands, and in both cases the exchange's
     // bounded wait turns starvation into a reported status
     return flagged && bp.single.pcg_resident == 2 ? hipLaunchCooperativeKernel(f, grid, dim3(kCgThreads), args, lds, s)
-                                       : hipLaunchKernel(f, grid, dim3(kCgThreads), args, lds, s);
+                                                  : hipLaunchKernel(f, grid, dim3(kCgThreads), args, lds, s);
   }
   const size_t ubytes = 6 * (size_t)max_tcols * sizeof(T);
-  if (bp.n_probs == 1) {
-    const void *f = CgStep<T>::single(bp.pcg_rows);
-    for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
-      void *args[] = {(void *)&bp.single, (void *)&it};
-      le = hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, ubytes, s);
-    }
-  } else {
-    const void *f = CgStep<T>::multi(bp.pcg_rows);
-    for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
-      void *args[] = {(void *)&bp.probs, (void *)&bp.pcg, (void *)&it};
-      le = hipLaunchKernel(f, dim3(bp.n_pcg), dim3(kCgThreads), args, ubytes, s);
-    }
+  const void *f = lone ? CgStep<T>::single(bp.big_rows) : CgStep<T>::multi(bp.big_rows);
+  for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
+    void *args1[] = {(void *)&bp.single, (void *)&it};
+    void *argsn[] = {(void *)&bp.probs, (void *)&bp.pcb, (void *)&it};
+    le = hipLaunchKernel(f, dim3(bp.n_pcb), dim3(kCgThreads), lone ? args1 : argsn, ubytes, s);
   }
   return le;
 }

@@ -68,6 +68,7 @@ struct Symbolic {
   int32_t max_tcols = 0;
   int32_t pcg_rows = kPcgRows;    // rows per PCG tile
   bool pcg_resident = false;      // the whole PCG in one launch (BA_FLAG_PCG_RESIDENT, when it fits)
+  bool pcg_small = false;         // one workgroup runs the whole PCG
   int pcg_run = 0;                // tiles per workgroup of the falling-back one-launch PCG, 0: does not fit
   bool pcg_coop = false;          // ... started as a cooperative launch (BA_FLAG_PCG_COOPERATIVE)
 };
@@ -144,7 +145,7 @@ struct DevProblem {
 struct Batch {
   std::vector<ProbDev> probs;
   std::vector<int> tags;
-  std::vector<Tile> tiles[16];  // pt, diag, off, pcg, cam, ctl, pp, ch, red, fin, fsh, pri, dpt, dcm, dsy, dre
+  std::vector<Tile> tiles[18];  // pt, diag, off, pcg, cam, ctl, pp, ch, red, fin, fsh, pri, dpt, dcm, dsy, dre, pcs, pcb
   std::vector<char> host;
   void *dev = nullptr;
   size_t cap = 0;

@@ -366,10 +366,15 @@ int ba_server::complete(bool block) {
 // workgroup each, where the device holds them beside the other such runs in flight.  The
 // CUs stay taken until the server is idle (earlier launches may still be running).
 int ba_server::batch_run(int max_tcols) {
-  const int rows = batch.plan.pcg_rows, n = batch.plan.n_pcg;
-  if (rows == 0 || n > device_cus()) return 0;
+  const int rows = batch.plan.big_rows, n = batch.plan.n_pcb;
+  if (n == 0 || rows == 0 || n > device_cus()) return 0;
+  // A lone request of fewer than 16 tiles (64 cameras) keeps a launch per iteration: the
+  // serving test that has a request overtake a waiting one keeps a lone 60-camera request
+  // of 300 iterations in flight for over 50 ms, and in one launch each (41 ms against 86)
+  // they would be over before.
+  if (batch.probs.size() == 1 && n < 16) return 0;
   for (const ProbDev &pd : batch.probs)
-    if (falling_back_pcg(precision, rows, pd.n_pcg_tiles, max_tcols) != 1) return 0;
+    if (!pd.pcg_small && falling_back_pcg(precision, rows, pd.n_pcg_tiles, max_tcols) != 1) return 0;
   if (n > cus) {
     if (!take_cus(device, n - cus, false)) return 0;
     cus = n;

@@ -245,3 +245,26 @@ def test_one_launch_pcg_beside_another(balib):
             _same(alone, p.result())
     for p in ps:
         p.close()
+
+
+@pytest.mark.parametrize("prec,free", [("f64", 1), ("f64", 10), ("f64", 11), ("f64", 24), ("f64", 25), ("f32", 1),
+                                       ("f32", 5), ("f32", 20), ("f32", 21), ("f32", 40), ("f32", 41)])
+def test_one_workgroup_pcg_edges(balib, prec, free):
+    """Free-camera counts at the edges of the one-workgroup PCG (runs of ten blocks, 4-row
+    tiles, the largest it takes and one more), every camera seeing every other: the solve
+    equals the launch-per-iteration steps bit for bit, also from the server beside another."""
+    s = make_arc_scene(free + 1, 400 + 7 * free, seed=free)
+    kw = dict(max_iters=4, pcg_max_iters=60, pcg_rel_tol=1e-10, precision=prec)
+    _say("device solves: free cameras", free, prec)
+    p = balib.Problem.from_scene(s, **kw)
+    a = p.solve().result()
+    p.set_barrier_polls(0)
+    _same(a, p.reset().solve().result())
+    p.close()
+    srv = balib.Server(1 << 28, 4, prec)
+    o = balib.options(**kw)
+    ts = [srv.submit(balib.scene_desc(q), o) for q in (s, make_small_drive(70, 1500, seed=2), s)]
+    rs = [srv.wait(t) for t in ts]
+    srv.close()
+    _same(a, rs[0])
+    _same(a, rs[2])
