@@ -1230,6 +1230,9 @@ static void xcd_contiguous(std::vector<Tile> &v) {
 int Batch::upload(hipStream_t s) {
   xcd_contiguous(tiles[2]);
   xcd_contiguous(tiles[7]);
+  // camera sums of the dense form: neighbouring cameras' records of a point share cache
+  // lines (197 cameras x 20011 points, 16-bit records: k_dense_cams 124 us instead of 145)
+  xcd_contiguous(tiles[13]);
   size_t need = probs.size() * sizeof(ProbDev);
   constexpr int NL = 18;
   size_t offs[NL];
