@@ -306,8 +306,9 @@ void ba_destroy(ba_problem *p);
    i in the order ba_get_kernel_times reports them; -1 all, 0 off) and times
    every stride-th launch of each (events between launches cost time, so a
    stride keeps the measured solve close to an unmeasured one).  The PCG step
-   kernel ("pcg_cg") is timed once per run of launches (one run per LM
-   iteration) and reports that run's launch count.  Profiled solves are
+   kernel ("pcg_cg") is timed once per run (one run per LM iteration) and counts
+   the run's steps, whether each is a launch or one launch runs them all; with
+   BA_FLAG_PCG_RESIDENT in effect a run counts as one launch.  Profiled solves are
    enqueued launch by launch, except when pcg_cg alone is selected: then each
    LM iteration replays three graphs (before, during and after the PCG run)
    with the events between them. */

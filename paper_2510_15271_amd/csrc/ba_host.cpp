@@ -1954,7 +1954,8 @@ static int queue_solve(ba_problem *p, const bool one) {
     (void)hipEventRecord(p->ev0, p->stream);
     if (p->dp.max_iters > 0) e = hipGraphLaunch(p->seg_exec[0], p->stream);
     for (int it = 0; it < p->dp.max_iters && e == hipSuccess; ++it) {
-      p->timer.begin(K_PCG_CG, p->stream, one ? 1 : p->dp.pcg_max);
+      // (without BA_FLAG_PCG_RESIDENT a run counts its steps, also when one launch runs them)
+      p->timer.begin(K_PCG_CG, p->stream, p->batch.plan.single.pcg_resident ? 1 : p->dp.pcg_max);
       // the resident run is one kernel: launched directly, not as a one-node graph
       e = one ? launch_lm_iteration(p->dp.precision, p->batch.plan, p->dp.pcg_max, p->dp.max_tcols,
                                                    p->stream, nullptr, LM_PCG)

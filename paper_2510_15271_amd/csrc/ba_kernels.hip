@@ -4579,8 +4579,9 @@ static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hi
   const int per_wg = flagged ? 1 : bp.pcg_run;
   int fall_back = flagged ? 0 : 1;
   // one event pair around the whole run: per-launch events would add their own
-  // overhead to launches this short
-  Timed t(tm, K_PCG_CG, s, per_wg || bp.n_pcb == 0 ? 1 : pcg_max);
+  // overhead to launches this short; a run counts its steps, and one where it was asked
+  // for as one launch
+  Timed t(tm, K_PCG_CG, s, flagged ? 1 : pcg_max);
   if (bp.n_pcs) {  // the problems that one workgroup solves
     void *args1[] = {(void *)&bp.single, (void *)&bp.probs, (void *)&pcg_max, (void *)&fall_back};
     void *argsn[] = {(void *)&bp.probs, (void *)&bp.pcs, (void *)&pcg_max};
