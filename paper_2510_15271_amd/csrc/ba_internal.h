@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <type_traits>
 
 namespace bax {
 
@@ -87,6 +88,31 @@ struct LMState {
 // Default of LMState::bar_polls: about a second of polling.
 constexpr int32_t kBarPollsDefault = 1 << 20;
 
+// A pointer into device memory as a device view holds it.  To a kernel that reads it from
+// the view, a plain pointer is generic: the compiler issues flat memory instructions, which
+// count against the LDS wait counter (an LDS read then waits for every one still in flight)
+// and cannot be scalar loads.  In device code this one is a global pointer: 10 cameras x 1000
+// points in FP64 4.10 -> 3.80 ms, 3000 cameras x 1.2M points 26.2 -> 25.7, most kernels a
+// few per cent.
+template <class T>
+struct Gp {
+#ifdef __HIP_DEVICE_COMPILE__
+  __attribute__((address_space(1))) T *p;
+#else
+  T *p;
+#endif
+  Gp() = default;
+  __host__ __device__ Gp(T *q) : p((decltype(p))q) {}
+  template <class U, class = std::enable_if_t<std::is_convertible<U *, T *>::value>>
+  __host__ __device__ Gp(const Gp<U> &o) : Gp((T *)(U *)o) {}
+  __host__ __device__ operator T *() const { return (T *)p; }
+  template <class U>
+  __host__ __device__ explicit operator U *() const {
+    return (U *)(T *)p;
+  }
+  __host__ __device__ T *operator->() const { return (T *)p; }
+};
+
 // Device view of one problem.  Arrays typed T hold the compute type of the
 // precision mode (double or float); S is the Jacobian storage type.
 struct ProbDev {
@@ -109,128 +135,128 @@ struct ProbDev {
   int32_t dn_tiles;      // camera tiles (kDnCams free cameras each)
   int32_t dn_pairs;      // tile pairs (a <= b)
   int32_t dn_split;      // point ranges per tile pair
-  const int32_t *dn_ts;  // [P][dn_tiles + 1] first record of each point in each camera tile
-  const int32_t *dn_rcam;  // [Nf] free camera of each record
-  const int2 *dn_crec;     // [Nf] (record, point) of each camera-major observation
-  const uint16_t *dn_mask; // [P][dn_tiles] bit c: camera c of the tile observes the point
-  void *dn_pfac;         // [P][9] T: L^-T (upper: 00 01 02 11 12 22) and h = L^-1 g_p of V*_j = L L^T
-  void *dn_part;         // [dn_pairs][dn_split][kDnRows^2] T: Z Z^T over one point range
+  Gp<const int32_t> dn_ts; // [P][dn_tiles + 1] first record of each point in each camera tile
+  Gp<const int32_t> dn_rcam; // [Nf] free camera of each record
+  Gp<const int2> dn_crec;  // [Nf] (record, point) of each camera-major observation
+  Gp<const uint16_t> dn_mask; // [P][dn_tiles] bit c: camera c of the tile observes the point
+  Gp<void> dn_pfac;      // [P][9] T: L^-T (upper: 00 01 02 11 12 22) and h = L^-1 g_p of V*_j = L L^T
+  Gp<void> dn_part;      // [dn_pairs][dn_split][kDnRows^2] T: Z Z^T over one point range
   // static structure
-  const void *K;                  // [C][4] T: fx, fy, cx, cy
-  const int32_t *free_idx;        // [C] free-camera index or -1
-  const int32_t *free_cam;        // [Cf] camera of each free index
-  const int32_t *obs_cam;         // [N] observations in (point, camera) order
-  const int32_t *obs_pt;          // [N]
-  const void *obs_uv;             // [N][2] T
-  const int32_t *pt_start;        // [P + 1]
-  const int32_t *obs_rpos;        // [N] record of each observation, -1 if its camera is fixed
-  uint8_t *obs_act;               // [N] 1: in the problem; 0: removed by culling (contributes
+  Gp<const void> K;               // [C][4] T: fx, fy, cx, cy
+  Gp<const int32_t> free_idx;     // [C] free-camera index or -1
+  Gp<const int32_t> free_cam;     // [Cf] camera of each free index
+  Gp<const int32_t> obs_cam;      // [N] observations in (point, camera) order
+  Gp<const int32_t> obs_pt;       // [N]
+  Gp<const void> obs_uv;          // [N][2] T
+  Gp<const int32_t> pt_start;     // [P + 1]
+  Gp<const int32_t> obs_rpos;     // [N] record of each observation, -1 if its camera is fixed
+  Gp<uint8_t> obs_act;            // [N] 1: in the problem; 0: removed by culling (contributes
                                   // nothing and is not counted as masked)
   // pair-list form: records are camera-major
-  const int32_t *cam_obs;         // [Nf] observation of each camera-major record
-  const int32_t *cam_obs_start;   // [Cf + 1] records of each free camera
-  const int32_t *up_pair_start;   // [n_up + 1]
-  const int2 *pairs;              // (c_a, c_b): records of one point in cameras a < b
+  Gp<const int32_t> cam_obs;      // [Nf] observation of each camera-major record
+  Gp<const int32_t> cam_obs_start; // [Cf + 1] records of each free camera
+  Gp<const int32_t> up_pair_start; // [n_up + 1]
+  Gp<const int2> pairs;           // (c_a, c_b): records of one point in cameras a < b
   // point-chunk form: records are point-major; a chunk's entries are runs of at
   // most kChSubItems items of one S block (diagonal: local observation; upper:
   // local observation pair p | q << 16), diagonal entries first
-  const int32_t *ch_pt;           // [n_ch + 1] point range of each chunk
-  const int32_t *ch_f0;           // [n_ch + 1] record range of each chunk
-  const int32_t *ch_ent;          // [n_ch + 1] entry range of each chunk
-  const int32_t *ch_cam_start;    // [n_ch + 1] range in ch_cam
-  const int32_t *ch_cam;          // cameras (caller's index) of each chunk's entries
-  const int32_t *ent_tgt;         // target block: a < Cf diagonal of camera a, Cf + u upper block u
-  const int32_t *ent_cam;         // chunk-local camera whose rotation the entry needs
-  const int32_t *ent_slot;        // position of the entry's partial in part_d / part_o (its
+  Gp<const int32_t> ch_pt;        // [n_ch + 1] point range of each chunk
+  Gp<const int32_t> ch_f0;        // [n_ch + 1] record range of each chunk
+  Gp<const int32_t> ch_ent;       // [n_ch + 1] entry range of each chunk
+  Gp<const int32_t> ch_cam_start; // [n_ch + 1] range in ch_cam
+  Gp<const int32_t> ch_cam;       // cameras (caller's index) of each chunk's entries
+  Gp<const int32_t> ent_tgt;      // target block: a < Cf diagonal of camera a, Cf + u upper block u
+  Gp<const int32_t> ent_cam;      // chunk-local camera whose rotation the entry needs
+  Gp<const int32_t> ent_slot;     // position of the entry's partial in part_d / part_o (its
                                   // position in its block's list, upper blocks counted from 0)
-  const int32_t *ent_start;       // [n_ent] first item; item h of the entry at ent_start + h * kEntSlice
-  const uint8_t *ent_len;         // [n_ent] items
-  const uint32_t *ent_items;      // per chunk, slices of kEntSlice entries: [slice][h][entry of the slice]
-  const int32_t *blk_start;       // [Cf + n_up + 1] entries of each block, in chunk order
+  Gp<const int32_t> ent_start;    // [n_ent] first item; item h of the entry at ent_start + h * kEntSlice
+  Gp<const uint8_t> ent_len;      // [n_ent] items
+  Gp<const uint32_t> ent_items;   // per chunk, slices of kEntSlice entries: [slice][h][entry of the slice]
+  Gp<const int32_t> blk_start;    // [Cf + n_up + 1] entries of each block, in chunk order
   int32_t n_dent;                 // diagonal entries (part_d rows)
-  const int32_t *up_pos;          // [n_up] block (a, b) in S
-  const int32_t *up_tpos;         // [n_up] block (b, a) in S
-  const int32_t *diag_pos;        // [Cf]
-  const int32_t *S_rowptr;        // [Cf + 1]
-  const int32_t *S_col;           // [nnzb]
-  const int32_t *tcol;            // [n_pcg_tiles][max_tcols] distinct columns read by each PCG tile, -1 padded
-  const int32_t *S_lcol;          // [nnzb] position of each block's column in its tile's list
+  Gp<const int32_t> up_pos;       // [n_up] block (a, b) in S
+  Gp<const int32_t> up_tpos;      // [n_up] block (b, a) in S
+  Gp<const int32_t> diag_pos;     // [Cf]
+  Gp<const int32_t> S_rowptr;     // [Cf + 1]
+  Gp<const int32_t> S_col;        // [nnzb]
+  Gp<const int32_t> tcol;         // [n_pcg_tiles][max_tcols] distinct columns read by each PCG tile, -1 padded
+  Gp<const int32_t> S_lcol;       // [nnzb] position of each block's column in its tile's list
   // state, double-buffered (LMState::cur selects the accepted copy)
-  double *pose[2];                // [C][12]: R row-major, then t
-  double *X[2];                   // [P][3]
+  Gp<double> pose[2];             // [C][12]: R row-major, then t
+  Gp<double> X[2];                // [P][3]
   // linearisation and Schur complement
-  void *lin;                      // [Nf] LinRec<T, S>
-  void *part_d;                   // [diagonal entries][54] T: U, Y W^T (upper 21 each), g_c, Y g_p
-  void *part_o;                   // [upper entries][36] T: sum Y W^T of the entry
-  double *row_tot;                // [Cf][54] camera-row sums of the diagonal partials
+  Gp<void> lin;                   // [Nf] LinRec<T, S>
+  Gp<void> part_d;                // [diagonal entries][54] T: U, Y W^T (upper 21 each), g_c, Y g_p
+  Gp<void> part_o;                // [upper entries][36] T: sum Y W^T of the entry
+  Gp<double> row_tot;             // [Cf][54] camera-row sums of the diagonal partials
   // relative-pose terms (FP64): the absolute prior's weight, the pairs (i, j) with
   // their measured A_ij = T_i T_j^-1 and rotation / translation weights (sequential
   // priors or pose-graph edges), per-camera U (21) and g (6) contributions, per-pair
   // off-diagonal blocks J_i^T W J_j oriented as the upper block of S
   double prior_abs;
   int32_t prior_on, n_pp, n_pri_tiles, pad1;
-  double *part_prior;             // [2][n_pri_tiles] prior cost at the current and trial poses
-  const double *pose0;            // [C][12] the initial poses (prior anchors)
-  const int2 *pp_cam;             // [n_pp] (i, j), caller's camera indices, i != j
-  const double *pp_meas;          // [n_pp][12] measured A_ij, R row-major then t
-  const double *pp_w;             // [n_pp][2] weights of the 9 rotation and 3 translation entries
-  const int32_t *pp_up;           // [n_pp] upper block of (free i, free j), or -1
-  const int32_t *cam_pp_start;    // [Cf + 1]
-  const int32_t *cam_pp;          // pairs of each free camera, ascending
-  double *prior_diag;             // [Cf][27]
-  double *prior_off;              // [n_pp][36]
+  Gp<double> part_prior;          // [2][n_pri_tiles] prior cost at the current and trial poses
+  Gp<const double> pose0;         // [C][12] the initial poses (prior anchors)
+  Gp<const int2> pp_cam;          // [n_pp] (i, j), caller's camera indices, i != j
+  Gp<const double> pp_meas;       // [n_pp][12] measured A_ij, R row-major then t
+  Gp<const double> pp_w;          // [n_pp][2] weights of the 9 rotation and 3 translation entries
+  Gp<const int32_t> pp_up;        // [n_pp] upper block of (free i, free j), or -1
+  Gp<const int32_t> cam_pp_start; // [Cf + 1]
+  Gp<const int32_t> cam_pp;       // pairs of each free camera, ascending
+  Gp<double> prior_diag;          // [Cf][27]
+  Gp<double> prior_off;           // [n_pp][36]
   int32_t prior_abs_from;         // the absolute prior covers nodes [prior_abs_from, prior_nodes)
   int32_t prior_nodes;
   // vehicle-rig problems: rig_mode 1 is the view over composed cameras (f, c), camera
   // f * n_rigcam + c, whose S blocks are formed undamped; rig_mode 2 is the view over the
   // rig unknowns (vehicle poses, then extrinsics), whose reduced system the PCG solves
   int32_t rig_mode, n_frames, n_rigcam, pad2;
-  double *Ucam;                   // (1) [C][21] undamped U of each composed camera
-  double *rig_pose[2];            // (1) [n_frames + n_rigcam][12] rig poses (the rig view's pose)
-  const void *rig_x, *rig_gc, *rig_Dc;  // (1) the rig view's x, g and D
-  const int32_t *rig_free_idx;    // (1) rig node -> free rig block
-  const int32_t *rb_start;        // (2) [nnzb + 1] contributions of camera S blocks to each rig block
-  const int32_t *rb_pos;          // (2) camera S block of each contribution
-  const int32_t *rb_lr;           // (2) (left rig camera + 1) | (right rig camera + 1) << 16; 0: identity
-  const int32_t *rb_diag;         // (2) [nnzb] row of a diagonal rig block, -1 for the others
-  const int32_t *rs_blk;          // (2) [nnzb + 1] segments of each rig block's contribution list
-  const int32_t *rs_c0;           // (2) [n_seg + 1] first contribution of each segment (<= kRigSeg each)
-  double *rpart;                  // (2) [n_seg][36] segment sums
+  Gp<double> Ucam;                // (1) [C][21] undamped U of each composed camera
+  Gp<double> rig_pose[2];         // (1) [n_frames + n_rigcam][12] rig poses (the rig view's pose)
+  Gp<const void> rig_x, rig_gc, rig_Dc; // (1) the rig view's x, g and D
+  Gp<const int32_t> rig_free_idx; // (1) rig node -> free rig block
+  Gp<const int32_t> rb_start;     // (2) [nnzb + 1] contributions of camera S blocks to each rig block
+  Gp<const int32_t> rb_pos;       // (2) camera S block of each contribution
+  Gp<const int32_t> rb_lr;        // (2) (left rig camera + 1) | (right rig camera + 1) << 16; 0: identity
+  Gp<const int32_t> rb_diag;      // (2) [nnzb] row of a diagonal rig block, -1 for the others
+  Gp<const int32_t> rs_blk;       // (2) [nnzb + 1] segments of each rig block's contribution list
+  Gp<const int32_t> rs_c0;        // (2) [n_seg + 1] first contribution of each segment (<= kRigSeg each)
+  Gp<double> rpart;               // (2) [n_seg][36] segment sums
   int32_t n_rig_seg, pad3;
-  double *rdiag;                  // (2) [Cf][36] undamped diagonal rig blocks
-  const int32_t *rr_start;        // (2) [Cf + 1] composed cameras of each rig row
-  const int32_t *rr_cam;
-  const void *cam_S, *cam_gc, *cam_brhs;  // (2) the camera view's S, g and b
-  const double *cam_U;            // (2) the camera view's Ucam
-  void *Q;                        // [Nf][6] T: J_p,k V*_j^-1 (2x3), camera-major
-  void *V, *gp, *Dp, *Vinv;       // [P][6], [P][3], [P][3], [P][6] T
-  void *gc, *Dc, *brhs;           // [Cf][6] T
-  void *S;                        // [nnzb][36] T
-  double *Minv;                   // [Cf][36]
-  void *x, *r, *z, *p0, *p1, *q;  // [6 Cf] T
+  Gp<double> rdiag;               // (2) [Cf][36] undamped diagonal rig blocks
+  Gp<const int32_t> rr_start;     // (2) [Cf + 1] composed cameras of each rig row
+  Gp<const int32_t> rr_cam;
+  Gp<const void> cam_S, cam_gc, cam_brhs; // (2) the camera view's S, g and b
+  Gp<const double> cam_U;         // (2) the camera view's Ucam
+  Gp<void> Q;                     // [Nf][6] T: J_p,k V*_j^-1 (2x3), camera-major
+  Gp<void> V, gp, Dp, Vinv;       // [P][6], [P][3], [P][3], [P][6] T
+  Gp<void> gc, Dc, brhs;          // [Cf][6] T
+  Gp<void> S;                     // [nnzb][36] T
+  Gp<double> Minv;                // [Cf][36]
+  Gp<void> x, r, z, p0, p1, q;    // [6 Cf] T
   // one-reduction PCG form: u = M^-1 r, w = S u, s = S p; two buffers each (parity)
-  void *cg_r[2], *cg_u[2], *cg_w[2], *cg_s[2];
+  Gp<void> cg_r[2], cg_u[2], cg_w[2], cg_s[2];
   // reductions (one partial per tile, summed in a fixed order)
-  double *part_lin_cost;          // [n_pt_tiles]
-  int32_t *part_masked;           // [n_pt_tiles]
-  double *part_sq;                // [n_pt_tiles]
-  double *part_trial_cost;        // [n_pt_tiles]
-  int32_t *part_trial_masked;     // [n_pt_tiles]
-  double *part_dl_pt;             // [n_pt_tiles]
-  double *part_dl_cam;            // [n_cam_tiles]
-  double *part_rz0;               // [Cf]
-  double *part_bb;                // [Cf]
-  double *part_rz[2];             // [n_pcg_tiles]
-  double *part_pq;                // [n_pcg_tiles]
-  double *part_cg[2];             // [3][n_pcg_tiles] r.u, w.u, r.r partials by parity
-  uint64_t *cg_xw[2];             // [6 Cf][words of T] resident PCG: stamped w by parity (see k_cg_run)
-  uint32_t *cg_dec;               // resident PCG that may fall back: the decision word
-  uint64_t *cg_xp[2];             // [6][n_pcg_tiles] ... stamped words of the r.u, w.u, r.r partials
-  double *part_rr;                // [n_pcg_tiles]
-  int32_t *part_cull;             // [n_pt_tiles][2] active observations, points with one, after culling
-  LMState *st;
-  double *iter_cost;              // [max_iters + 1]
-  int32_t *iter_pcg;              // [max_iters]
+  Gp<double> part_lin_cost;       // [n_pt_tiles]
+  Gp<int32_t> part_masked;        // [n_pt_tiles]
+  Gp<double> part_sq;             // [n_pt_tiles]
+  Gp<double> part_trial_cost;     // [n_pt_tiles]
+  Gp<int32_t> part_trial_masked;  // [n_pt_tiles]
+  Gp<double> part_dl_pt;          // [n_pt_tiles]
+  Gp<double> part_dl_cam;         // [n_cam_tiles]
+  Gp<double> part_rz0;            // [Cf]
+  Gp<double> part_bb;             // [Cf]
+  Gp<double> part_rz[2];          // [n_pcg_tiles]
+  Gp<double> part_pq;             // [n_pcg_tiles]
+  Gp<double> part_cg[2];          // [3][n_pcg_tiles] r.u, w.u, r.r partials by parity
+  Gp<uint64_t> cg_xw[2];          // [6 Cf][words of T] resident PCG: stamped w by parity (see k_cg_run)
+  Gp<uint32_t> cg_dec;            // resident PCG that may fall back: the decision word
+  Gp<uint64_t> cg_xp[2];          // [6][n_pcg_tiles] ... stamped words of the r.u, w.u, r.r partials
+  Gp<double> part_rr;             // [n_pcg_tiles]
+  Gp<int32_t> part_cull;          // [n_pt_tiles][2] active observations, points with one, after culling
+  Gp<LMState> st;
+  Gp<double> iter_cost;           // [max_iters + 1]
+  Gp<int32_t> iter_pcg;           // [max_iters]
 };
 
 // Tile lists of one batch (device pointers) and their lengths.

@@ -43,15 +43,17 @@ const char *const kKernelNames[K_NUM_KERNELS] = {
     "schur_reduce", "schur_rows", "schur_finish", "prior_lin", "prior_apply", "cull", "rig_blocks",
     "rig_rows", "rig_update", "prior_cost", "dense_prep", "dense_cams", "dense_schur", "dense_reduce"};
 
-// A pointer read from a problem's device view is generic to the compiler, which then
-// issues flat memory instructions; a flat access also counts against the LDS wait
-// counter, so an LDS read waits for every such access still in flight.  Accesses made
-// through as_global(p) are global ones.
+// A global pointer, so that the accesses made through it are global ones (see Gp) also
+// where it went through a generic one.
 template <class T>
 using global_t = __attribute__((address_space(1))) T;
 template <class T>
 __device__ __forceinline__ global_t<T> *as_global(T *p) {
   return (global_t<T> *)p;
+}
+template <class T>
+__device__ __forceinline__ global_t<T> *as_global(const Gp<T> &p) {
+  return (global_t<T> *)(T *)p;
 }
 
 // ------------------------------------------------------------------ storage codecs
