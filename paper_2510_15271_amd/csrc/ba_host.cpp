@@ -949,6 +949,7 @@ int DevProblem::init(const Symbolic &sy, const ba_problem_desc *d, const ba_opti
   pd.dn_tiles = sy.dense ? sy.dn_tiles : 0;
   pd.dn_pairs = sy.dense ? sy.dn_tiles * (sy.dn_tiles + 1) / 2 : 0;
   pd.dn_split = sy.dense ? sy.dn_split : 0;
+  pd.dn_quarter = sy.dense && sy.dn_tiles * (sy.dn_tiles + 1) / 2 * sy.dn_split <= kDnQuarterWgs ? 1 : 0;
   pd.n_up = sy.n_up;
   pd.nnzb = sy.nnzb;
   pd.n_pt_tiles = (P + sy.pt_tile - 1) / sy.pt_tile;
@@ -1189,7 +1190,11 @@ void Batch::add(const ProbDev &pd, int slot_tag) {
   if (pd.dense) {
     for (int t = 0; t < pd.n_pt_tiles; ++t) tiles[12].push_back(Tile{pi, t});
     for (int a = 0; a < pd.Cf; ++a) tiles[13].push_back(Tile{pi, a});
-    for (int t = 0; t < pd.dn_pairs * pd.dn_split; ++t) tiles[14].push_back(Tile{pi, t});
+    if (pd.dn_quarter)
+      for (int t = 0; t < 4 * pd.dn_pairs * pd.dn_split; ++t) tiles[18].push_back(Tile{pi, t});
+    else
+      for (int r = 0; r < pd.dn_split; ++r)  // by range: an XCD's workgroups share the records
+        for (int t = 0; t < pd.dn_pairs; ++t) tiles[14].push_back(Tile{pi, t * pd.dn_split + r});
     for (int t = 0; t < pd.dn_pairs * kDnCams; ++t) tiles[15].push_back(Tile{pi, t});
     for (int t = 0; t < pd.n_fsh_tiles; ++t) tiles[10].push_back(Tile{pi, t});
   } else if (pd.chunked) {
@@ -1233,8 +1238,9 @@ int Batch::upload(hipStream_t s) {
   // camera sums of the dense form: neighbouring cameras' records of a point share cache
   // lines (197 cameras x 20011 points, 16-bit records: k_dense_cams 124 us instead of 145)
   xcd_contiguous(tiles[13]);
+  xcd_contiguous(tiles[14]);
   size_t need = probs.size() * sizeof(ProbDev);
-  constexpr int NL = 18;
+  constexpr int NL = 19;
   size_t offs[NL];
   for (int i = 0; i < NL; ++i) {
     need = (need + 255) & ~size_t(255);
@@ -1259,10 +1265,10 @@ int Batch::upload(hipStream_t s) {
   plan.probs = (const ProbDev *)b;
   const Tile **dst[NL] = {&plan.pt, &plan.diag, &plan.off, &plan.pcg, &plan.cam, &plan.ctl,
                           &plan.pp, &plan.ch, &plan.red, &plan.fin, &plan.fsh, &plan.pri,
-                          &plan.dpt, &plan.dcm, &plan.dsy, &plan.dre, &plan.pcs, &plan.pcb};
+                          &plan.dpt, &plan.dcm, &plan.dsy, &plan.dre, &plan.pcs, &plan.pcb, &plan.dsq};
   int32_t *cnt[NL] = {&plan.n_pt, &plan.n_diag, &plan.n_off, &plan.n_pcg, &plan.n_cam, &plan.n_ctl,
                       &plan.n_pp, &plan.n_ch, &plan.n_red, &plan.n_fin, &plan.n_fsh, &plan.n_pri,
-                      &plan.n_dpt, &plan.n_dcm, &plan.n_dsy, &plan.n_dre, &plan.n_pcs, &plan.n_pcb};
+                      &plan.n_dpt, &plan.n_dcm, &plan.n_dsy, &plan.n_dre, &plan.n_pcs, &plan.n_pcb, &plan.n_dsq};
   for (int i = 0; i < NL; ++i) {
     *dst[i] = (const Tile *)(b + offs[i]);
     *cnt[i] = (int32_t)tiles[i].size();

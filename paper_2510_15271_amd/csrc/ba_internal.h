@@ -55,6 +55,11 @@ constexpr int kDnRows = 6 * kDnCams;
 constexpr int kDnMaxCams = 1024;     // free cameras beyond which the dense form is not used
 constexpr int kDnTargetWgs = 256;   // workgroups per problem the point ranges aim at
 constexpr int kDnRangePts = 2048;   // points per range at most
+// Up to so many (tile pair, point range)s, half of the CUs, a workgroup takes a quarter of
+// one.  k_dense_schur, whole / quarters: 23 free cameras, 1500 points (15 of them) FP32 55 /
+// 28 us, FP64 107 / 58; 59 cameras, 3000 points (110) FP32 58 / 41, FP64 107 / 98; 59 cameras,
+// 5000 points (190) FP32 54 / 52, FP64 104 / 138; 119 cameras, 10000 points (288) FP64 710 / 956.
+constexpr int kDnQuarterWgs = 128;
 
 constexpr double kLambdaMin = 1e-12;
 constexpr double kLambdaMax = 1e16;
@@ -135,6 +140,7 @@ struct ProbDev {
   int32_t dn_tiles;      // camera tiles (kDnCams free cameras each)
   int32_t dn_pairs;      // tile pairs (a <= b)
   int32_t dn_split;      // point ranges per tile pair
+  int32_t dn_quarter;    // 1: a workgroup of k_dense_schur takes a quarter of a tile pair
   Gp<const int32_t> dn_ts; // [P][dn_tiles + 1] first record of each point in each camera tile
   Gp<const int32_t> dn_rcam; // [Nf] free camera of each record
   Gp<const int2> dn_crec;  // [Nf] (record, point) of each camera-major observation
@@ -271,6 +277,8 @@ struct BatchPlan {
   // the problems whose PCG one workgroup runs, and the PCG tiles of the others
   const Tile *pcs, *pcb;
   int32_t n_pcs, n_pcb;
+  const Tile *dsq;  // dense form: quarters of (tile pair, range), for problems with dn_quarter
+  int32_t n_dsq;
   int32_t n_probs;
   int32_t pcg_rows;  // rows per PCG tile shared by every problem of the batch, 0 if mixed
   int32_t big_rows;  // ... by those whose PCG takes more than one workgroup

@@ -4064,18 +4064,21 @@ __global__ __launch_bounds__(256) void k_dense_prep(const ProbDev *__restrict__ 
   pf[8] = T(m20 * g0 + m21 * g1 + m22 * g2);
 }
 
-// Z (6x3) of one observation: W = J_c^T J_p times the point's L^-T (lt, upper).
+// Row m of Z (6x3) of one observation: W = J_c^T J_p times the point's L^-T (lt, upper).
+// J_c holds a structural zero in each of its first two columns (see jc_from).
+template <class T>
+__device__ inline void dense_z_row(int m, const T Jc[12], const T Jp[6], const T lt[6], T Z[3]) {
+  const T w0 = m == 0 ? Jc[0] * Jp[0] : m == 1 ? Jc[7] * Jp[3] : Jc[m] * Jp[0] + Jc[6 + m] * Jp[3];
+  const T w1 = m == 0 ? Jc[0] * Jp[1] : m == 1 ? Jc[7] * Jp[4] : Jc[m] * Jp[1] + Jc[6 + m] * Jp[4];
+  const T w2 = m == 0 ? Jc[0] * Jp[2] : m == 1 ? Jc[7] * Jp[5] : Jc[m] * Jp[2] + Jc[6 + m] * Jp[5];
+  Z[0] = w0 * lt[0];
+  Z[1] = w0 * lt[1] + w1 * lt[3];
+  Z[2] = w0 * lt[2] + w1 * lt[4] + w2 * lt[5];
+}
 template <class T>
 __device__ inline void dense_z(const T Jc[12], const T Jp[6], const T lt[6], T Z[18]) {
 #pragma unroll
-  for (int m = 0; m < 6; ++m) {
-    const T w0 = Jc[m] * Jp[0] + Jc[6 + m] * Jp[3];
-    const T w1 = Jc[m] * Jp[1] + Jc[6 + m] * Jp[4];
-    const T w2 = Jc[m] * Jp[2] + Jc[6 + m] * Jp[5];
-    Z[3 * m] = w0 * lt[0];
-    Z[3 * m + 1] = w0 * lt[1] + w1 * lt[3];
-    Z[3 * m + 2] = w0 * lt[2] + w1 * lt[4] + w2 * lt[5];
-  }
+  for (int m = 0; m < 6; ++m) dense_z_row(m, Jc, Jp, lt, Z + 3 * m);
 }
 
 // Camera sums of the dense form, one workgroup per free camera over its observations
@@ -4186,6 +4189,7 @@ struct DnMma<float, float> {
 template <>
 struct DnMma<float, _Float16> {
   using E = _Float16;
+  using E2 = _Float16 __attribute__((ext_vector_type(2)));
   using V = dn_f4;
   static constexpr int KI = 32, PC = 32;
   static constexpr bool row_major_d = true;
@@ -4196,6 +4200,7 @@ struct DnMma<float, _Float16> {
 template <>
 struct DnMma<float, bf16s> {
   using E = __bf16;
+  using E2 = __bf16 __attribute__((ext_vector_type(2)));
   using V = dn_f4;
   static constexpr int KI = 32, PC = 32;
   static constexpr bool row_major_d = true;
@@ -4203,20 +4208,27 @@ struct DnMma<float, bf16s> {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(*(const dn_b8 *)a, *(const dn_b8 *)b, c, 0, 0, 0);
   }
 };
-// LDS layout of a Z tile in k_dense_schur: k-value kk of row r at
-// (kk / KI) * kDnRows * RS + r * RS + kk % KI, where a camera's six rows are spread
-// (row m of camera slot a at kDnCams * m + a), so that the 16 cameras a wave stores at
-// once fall in distinct banks, and a row holds KI values plus, for 16-bit operands, 8 of
-// padding, so that the 16-byte operand reads of 16 consecutive rows do not share banks.
+// LDS layout of a Z tile of HC cameras in k_dense_schur: k-value kk of row r lies in block
+// kk / KI (6 HC rows of KI values) at dn_at(r, kk % KI), where a camera's six rows are
+// spread (row m of camera slot a at HC * m + a), so that the 16 cameras a wave stores at
+// once fall in distinct banks.  16-bit rows are 64 bytes: their four 16-byte pieces are
+// permuted by the row's bits 2 and 3, so that neither the 16-byte operand reads of 16
+// consecutive rows nor the stores of 16 cameras by 4 point pairs share banks (padding the
+// rows instead took 46 KB per workgroup, three to a CU; this takes 37 KB, four).
 template <class T, class S>
-constexpr int dn_row_stride() {
-  return DnMma<T, S>::KI + (sizeof(typename DnMma<T, S>::E) == 2 ? 8 : 0);
+__device__ inline int dn_at(int r, int k) {
+  constexpr int KI = DnMma<T, S>::KI;
+  return r * KI + (sizeof(typename DnMma<T, S>::E) == 2 ? k ^ ((r >> 2 & 3) << 3) : k);
 }
-// Dynamic LDS of k_dense_schur: two Z tiles of 3 PC k-values by kDnRows rows.
-template <class T, class S>
+// Z tile buffers of a workgroup: with two, a chunk is written while the one before is read.
+template <int HC>
+constexpr int dn_bufs() {
+  return HC == kDnCams ? 1 : 2;
+}
+// Dynamic LDS of k_dense_schur: two Z tiles of 3 PC k-values by 6 HC rows per buffer.
+template <class T, class S, int HC = kDnCams>
 constexpr size_t dn_lds_bytes() {
-  return 2 * (size_t)(3 * DnMma<T, S>::PC / DnMma<T, S>::KI) * kDnRows * dn_row_stride<T, S>() *
-         sizeof(typename DnMma<T, S>::E);
+  return dn_bufs<HC>() * 2 * (size_t)(3 * DnMma<T, S>::PC) * 6 * HC * sizeof(typename DnMma<T, S>::E);
 }
 
 // Tile pair (ta <= tb) of a pair index, row-major over the upper triangle of nt tiles.
@@ -4230,41 +4242,59 @@ __device__ inline void dn_pair(int pair, int nt, int &ta, int &tb) {
   tb = a + rem;
 }
 
-// One (tile pair, point range): Z tiles in LDS laid out [k / KI][row][k % KI] so that
-// the 64 lanes of an operand load read one contiguous run; four waves, each a 48 x 48
-// quarter of the 96 x 96 product (3 x 3 MFMA tiles of 16 x 16).  Thread (point jl,
-// sub) owns camera slots sub, sub + SUB, ... of its point in each tile and writes their
-// Z blocks, or zeros where the camera does not see the point (the point's camera mask
-// gives presence and the record's place in the point's range).  The records of the next
-// chunk are loaded into registers before the current chunk's products, so their latency
-// hides behind the matrix cores.
-template <class T, class S>
-__global__ __launch_bounds__(256) void k_dense_schur(const ProbDev *__restrict__ probs,
+// One (tile pair, point range): Z tiles in LDS (dn_at), four waves, each a 48 x 48
+// quarter of the 96 x 96 product (3 x 3 MFMA tiles of 16 x 16).  A thread owns one camera
+// slot and PT consecutive points (two for 16-bit operands, stored as whole words) of both
+// tiles and writes their Z blocks, or zeros where the camera does not see the point (the
+// point's camera mask gives presence and the record's place in the point's range).  The
+// records of the next chunk are loaded into registers before the current chunk's products,
+// and what finds them (first record, mask) a chunk earlier, so that neither latency of
+// this two-step chain stands between the barriers.
+// HC = 8: a workgroup takes one 48 x 48 quarter of the tile pair (cameras 8 qa .. of tile
+// ta, 8 qb .. of tile tb; the nine MFMA tiles go round the four waves), for problems whose
+// tile pairs and ranges would leave most CUs idle: a chunk's products take a third of the
+// time, and quarters without cameras are left out.
+// Every element of the product is summed over the same points in the same order.
+// Bound: FP32 by the matrix cores (196 free cameras x 20011 points: 978 us, 659 of them
+// MFMA issue); 16-bit by the vector ALU that forms each Z block once per tile pair (276 us,
+// with 512 before: two points per thread stored as words instead of 16-bit values, one
+// 16-byte load per record, 32-bit offsets and four workgroups to a CU instead of three);
+// small problems by the chain of chunks (19 free cameras x 1777 points FP32 72 -> 28 us).
+template <class T, class S, int HC>
+__global__ __launch_bounds__(256, sizeof(T) == 4 ? 4 : 1) void k_dense_schur(const ProbDev *__restrict__ probs,
                                                      const Tile *__restrict__ tiles) {
   using M = DnMma<T, S>;
   using E = typename M::E;
   using V = typename M::V;
-  constexpr int KI = M::KI, PC = M::PC, K = 3 * PC, NKS = K / KI, SUB = 256 / PC, KL = KI / 4;
-  constexpr int NSLOT = kDnCams / SUB;  // camera slots of one point and tile per thread
-  constexpr int RS = dn_row_stride<T, S>(), BS = kDnRows * RS;  // row and k-block strides
+  constexpr int KI = M::KI, PC = M::PC, K = 3 * PC, NKS = K / KI, KL = KI / 4;
+  constexpr int PT = sizeof(E) == 2 ? 2 : 1;     // points per thread
+  constexpr int NT = PC / PT * HC;               // threads that stage one side
+  constexpr int NSD = NT == 256 ? 2 : 1;         // sides a thread stages
+  static_assert(NT == 256 || NT == 128, "every camera slot has a thread");
+  constexpr int NW = (7 * sizeof(S) + 3) / 4;    // words of a record's Jacobian values
+  constexpr int BS = 6 * HC * KI;                // values of a k-block
+  constexpr int NTL = HC == kDnCams ? 9 : 3;     // MFMA tiles per wave
   extern __shared__ __align__(16) double s_dyn[];
-  E *za = (E *)s_dyn;        // [NKS][kDnRows][RS]
-  E *zb = za + NKS * BS;     // the same for tile tb (unused when ta == tb)
-  __shared__ T s_R[2][kDnCams][9];
+  __shared__ T s_R[2][HC][9];
+  __shared__ __align__(16) T s_lt[2][PC][8];  // L^-T of a chunk's points, by parity of the chunk
   const Tile tl = tiles[blockIdx.x];
   const ProbDev &pd = probs[tl.prob];
   const LMState *st = pd.st;
   if (!lm_active(st)) return;
-  const int pair = tl.idx / pd.dn_split, split = tl.idx - pair * pd.dn_split;
+  const int part = HC == kDnCams ? tl.idx : tl.idx >> 2;  // (pair, range)
+  const int pair = part / pd.dn_split, split = part - pair * pd.dn_split;
   int ta, tb;
   dn_pair(pair, pd.dn_tiles, ta, tb);
-  const bool diag = ta == tb;
+  const int qa = HC == kDnCams ? 0 : (tl.idx >> 1) & 1, qb = HC == kDnCams ? 0 : tl.idx & 1;
+  const int ca = ta * kDnCams + HC * qa, cb = tb * kDnCams + HC * qb;  // first camera of each side
+  if (HC != kDnCams && (ca > cb || cb >= pd.Cf)) return;  // a transposed or an empty quarter
+  const bool diag = ca == cb;
   const int nsides = diag ? 1 : 2;
   const int nt = pd.dn_tiles, nt1 = pd.dn_tiles + 1;
   const int t = threadIdx.x;
-  if (t < 2 * kDnCams) {
-    const int side = t / kDnCams, la = t - kDnCams * side;
-    const int a = (side ? tb : ta) * kDnCams + la;
+  if (t < 2 * HC) {
+    const int side = t / HC, la = t - HC * side;
+    const int a = (side ? cb : ca) + la;
     T R[9];
     if (a < pd.Cf) {
       load_rot(pd.pose[st->cur] + 12 * pd.free_cam[a], R);
@@ -4277,68 +4307,105 @@ __global__ __launch_bounds__(256) void k_dense_schur(const ProbDev *__restrict__
   }
   const int j0 = (int)((int64_t)pd.P * split / pd.dn_split);
   const int j1 = (int)((int64_t)pd.P * (split + 1) / pd.dn_split);
-  const LinRec<T, S> *lin = (const LinRec<T, S> *)pd.lin;
-  const T *pf = (const T *)pd.dn_pfac;
   const int lane = t & 63, wv = t >> 6;
-  const int rb0 = 3 * (wv >> 1), cb0 = 3 * (wv & 1);
   const int li = lane & 15, lq = lane >> 4;
-  const int jl = t / SUB, sub = t - SUB * (t / SUB);
-  // the next chunk's records of this thread's camera slots (stored Jacobian values)
-  S nf[2][NSLOT][7];
-  bool npr[2][NSLOT];
-  T nlt[6];
-  auto fetch = [&](int jc) {
-    const int j = jc + jl;
+  const int side0 = NSD == 2 ? 0 : __builtin_amdgcn_readfirstlane(t / NT);  // the first side this wave stages
+  const int jl = PT * (t % NT / HC), la = t % HC;
+  // the range's first point and record: offsets from them fit 24 bits (at most kDnRangePts
+  // points of kDnMaxCams records)
+  static_assert((int64_t)kDnRangePts * (kDnMaxCams + 1) < 1 << 24, "24-bit products");
+  const int np = j1 - j0, rb = np ? pd.dn_ts[(size_t)j0 * nt1] : 0;
+  const LinRec<T, S> *lin = (const LinRec<T, S> *)pd.lin + rb;
+  const T *pf = (const T *)pd.dn_pfac + 9 * (size_t)j0;
+  const int32_t *ts = pd.dn_ts + (size_t)j0 * nt1;
+  const uint16_t *mask = pd.dn_mask + (size_t)j0 * nt;
+  // Addresses are a uniform base that moves with the chunk plus a thread's 32-bit offset
+  // (kept apart from the base, or each load would hold a 64-bit pointer of its own per thread).
+  auto at = [](const auto *base, uint32_t bytes) {
+    asm volatile("" : "+v"(bytes));
+    return (decltype(base))((const char *)base + bytes);
+  };
+  // first record and mask of this thread's points in the chunk to be fetched next, then
+  // that chunk's records (stored Jacobian values; pr: bit p for point p)
+  int mr[NSD][PT];
+  uint32_t mm[NSD][PT];
+  uint32_t nf[NSD][PT][NW] = {};
+  uint32_t pr[NSD];
+  const uint32_t ots = 4 * __umul24(jl, nt1), omk = 2 * __umul24(jl, nt);
+  auto find = [&](int jc) {
 #pragma unroll
-    for (int side = 0; side < 2; ++side)
+    for (int sd = 0; sd < NSD; ++sd)
 #pragma unroll
-      for (int q = 0; q < NSLOT; ++q) npr[side][q] = false;
-    if (j >= j1) return;
+      for (int p = 0; p < PT; ++p) {
+        const int side = side0 + sd, tt = side ? tb : ta;
+        mm[sd][p] = 0;
+        if (jl < np - jc - p && side < nsides) {
+          mr[sd][p] = *at(ts + (jc + p) * nt1 + tt, ots);
+          mm[sd][p] = *at(mask + (jc + p) * nt + tt, omk);
+        }
+      }
+  };
+  T lt = 0;  // this thread's value of L^-T of the chunk after next
+  const int lp = t / 6, lv = t - 6 * lp;
+  const uint32_t olt = (uint32_t)sizeof(T) * (9 * lp + lv);
+  auto factors = [&](int jc) {
+    if (lp < PC && lp < np - jc) lt = *at(pf + 9 * jc, olt);
+  };
+  auto fetch = [&] {
 #pragma unroll
-    for (int i = 0; i < 6; ++i) nlt[i] = pf[9 * (size_t)j + i];
+    for (int sd = 0; sd < NSD; ++sd) {
+      pr[sd] = 0;
 #pragma unroll
-    for (int side = 0; side < 2; ++side) {
-      if (side >= nsides) break;
-      const int tt = side ? tb : ta;
-      const int r0 = pd.dn_ts[(size_t)j * nt1 + tt];
-      const uint32_t mk = pd.dn_mask[(size_t)j * nt + tt];
+      for (int p = 0; p < PT; ++p) {
+        const int c = HC * (side0 + sd ? qb : qa) + la;  // camera slot of the tile
+        const uint32_t mk = mm[sd][p];
+        if ((mk >> c) & 1u) {
+          const int r = mr[sd][p] - rb + __popc(mk & ((1u << c) - 1u));
+          const uint32_t *w = (const uint32_t *)at(lin, __umul24(r, (uint32_t)sizeof(LinRec<T, S>)));
 #pragma unroll
-      for (int q = 0; q < NSLOT; ++q) {
-        const int la = sub + SUB * q;
-        if ((mk >> la) & 1u) {
-          const int r = r0 + __popc(mk & ((1u << la) - 1u));
-#pragma unroll
-          for (int i = 0; i < 7; ++i) nf[side][q][i] = lin[r].f[i];
-          npr[side][q] = true;
+          for (int i = 0; i < NW; ++i) nf[sd][p][i] = w[i];
+          pr[sd] |= 1u << p;
         }
       }
     }
   };
-  V acc[3][3];
+  // the wave's MFMA tiles: a 3 x 3 block of the 6 x 6, or every fourth of the 3 x 3
+  auto tile_r = [&](int x) { return HC == kDnCams ? 3 * (wv >> 1) + x / 3 : min(wv + 4 * x, 8) / 3; };
+  auto tile_c = [&](int x) { return HC == kDnCams ? 3 * (wv & 1) + x % 3 : min(wv + 4 * x, 8) % 3; };
+  V acc[NTL];
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
+  for (int x = 0; x < NTL; ++x)
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
+    for (int e = 0; e < 4; ++e) acc[x][e] = 0;
+  find(0);
+  fetch();
+  find(PC);
+  factors(0);
+  if (lp < PC) s_lt[0][lp][lv] = lt;
+  factors(PC);
+  int buf = 0, par = 0;
+  if (dn_bufs<HC>() == 2) __syncthreads();  // s_R and s_lt are visible
+  for (int jc = 0; jc < np; jc += PC) {
+    E *za = (E *)s_dyn + buf * 2 * NKS * BS;  // [NKS][6 HC][KI]
+    E *zb = za + NKS * BS;                    // the same for tile tb (unused when ta == tb)
+    if (dn_bufs<HC>() == 1) __syncthreads();  // the previous chunk's products are done (and s_R, s_lt are visible)
+    if (lp < PC) s_lt[par ^ 1][lp][lv] = lt;  // read after the next barrier
 #pragma unroll
-      for (int e = 0; e < 4; ++e) acc[r][c][e] = 0;
-  fetch(j0);
-  for (int jc = j0; jc < j1; jc += PC) {
-    __syncthreads();  // the previous chunk's products are done (and s_R is visible)
-#pragma unroll
-    for (int side = 0; side < 2; ++side) {
+    for (int sd = 0; sd < NSD; ++sd) {
+      const int side = side0 + sd;
       if (side >= nsides) break;
       E *z = side ? zb : za;
-#pragma unroll
-      for (int q = 0; q < NSLOT; ++q) {
-        const int la = sub + SUB * q;
+      if constexpr (PT == 1) {
         T Z[18];
-        if (npr[side][q]) {
+        if (pr[sd]) {
+          S fs[8];
+          __builtin_memcpy(fs, nf[sd][0], NW * 4);
           T f[7], Jc[12], Jp[6];
 #pragma unroll
-          for (int i = 0; i < 7; ++i) f[i] = Codec<S>::dec(nf[side][q][i]);
+          for (int i = 0; i < 7; ++i) f[i] = Codec<S>::dec(fs[i]);
           jc_from(f, Jc);
           jp_from(f, &s_R[side][la][0], Jp);
-          dense_z(Jc, Jp, nlt, Z);
+          dense_z(Jc, Jp, s_lt[par][jl], Z);
         } else {
 #pragma unroll
           for (int i = 0; i < 18; ++i) Z[i] = T(0);
@@ -4347,39 +4414,80 @@ __global__ __launch_bounds__(256) void k_dense_schur(const ProbDev *__restrict__
         for (int m = 0; m < 6; ++m)
 #pragma unroll
           for (int c = 0; c < 3; ++c) {
-            const int kk = 3 * jl + c, row = kDnCams * m + la;
-            z[(kk / KI) * BS + row * RS + (kk % KI)] = E(Z[3 * m + c]);
+            const int kk = 3 * jl + c;
+            z[(kk / KI) * BS + dn_at<T, S>(HC * m + la, kk % KI)] = E(Z[3 * m + c]);
           }
+      } else {
+        // Six consecutive k-values per row, three words: the first point's first two, its last
+        // with the second's first, the second's last two.  An absent point's values are
+        // formed too and masked out; a word's values are rounded to T before they are packed
+        // (the 16-bit rounding is not fused with the product).
+        using E2 = typename M::E2;
+        T last[6];  // the first point's last value of each row
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          S fs[8];
+          __builtin_memcpy(fs, nf[sd][p], NW * 4);
+          T f[7], Jc[12], Jp[6], l[6];
+#pragma unroll
+          for (int i = 0; i < 7; ++i) f[i] = Codec<S>::dec(fs[i]);
+#pragma unroll
+          for (int i = 0; i < 6; ++i) l[i] = s_lt[par][jl + p][i];
+          jc_from(f, Jc);
+          jp_from(f, &s_R[side][la][0], Jp);
+          const uint32_t k0 = pr[sd] & 1u ? ~0u : 0u, k1 = pr[sd] & 2u ? ~0u : 0u;
+          auto put = [&](int m, int c, T z0, T z1, uint32_t keep) {
+            const int kk = 3 * jl + 2 * c;
+            asm("" : "+v"(z0), "+v"(z1));
+            const E2 v = {E(z0), E(z1)};
+            *(uint32_t *)&z[(kk / KI) * BS + dn_at<T, S>(HC * m + la, kk % KI)] = __builtin_bit_cast(uint32_t, v) & keep;
+          };
+#pragma unroll
+          for (int m = 0; m < 6; ++m) {
+            T Z[3];
+            dense_z_row(m, Jc, Jp, l, Z);
+            if (p == 0) {
+              put(m, 0, Z[0], Z[1], k0);
+              last[m] = Z[2];
+            } else {
+              put(m, 1, last[m], Z[0], (k0 & 0xffffu) | (k1 & 0xffff0000u));
+              put(m, 2, Z[1], Z[2], k1);
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);  // one point after the other: both at once do not fit the registers
+        }
       }
     }
     __syncthreads();
-    if (jc + PC < j1) fetch(jc + PC);  // in flight during the products below
+    if (jc + PC < np) {  // in flight during the products below
+      fetch();
+      find(jc + 2 * PC);
+      factors(jc + 2 * PC);
+    }
+    par ^= 1;
     const E *zbb = diag ? za : zb;
 #pragma unroll
     for (int ks = 0; ks < NKS; ++ks) {
-      const E *ab = za + ks * BS + li * RS + lq * KL;
-      const E *bb = zbb + ks * BS + li * RS + lq * KL;
+      const int at = ks * BS + dn_at<T, S>(li, lq * KL);
 #pragma unroll
-      for (int r = 0; r < 3; ++r)
-#pragma unroll
-        for (int c = 0; c < 3; ++c)
-          acc[r][c] = M::mma(ab + 16 * (rb0 + r) * RS, bb + 16 * (cb0 + c) * RS, acc[r][c]);
+      for (int x = 0; x < NTL; ++x)  // (three also for the waves that keep two: no branch)
+          acc[x] = M::mma(za + at + 16 * tile_r(x) * KI, zbb + at + 16 * tile_c(x) * KI, acc[x]);
     }
+    if (dn_bufs<HC>() == 2) buf ^= 1;
   }
-  T *out = (T *)pd.dn_part + (size_t)tl.idx * kDnRows * kDnRows;
+  T *out = (T *)pd.dn_part + (size_t)part * kDnRows * kDnRows;
 #pragma unroll
-  for (int r = 0; r < 3; ++r)
+  for (int x = 0; x < NTL; ++x)
 #pragma unroll
-    for (int c = 0; c < 3; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        // LDS rows back to camera-major rows (6 per camera)
-        const int prow = 16 * (rb0 + r) + (M::row_major_d ? 4 * lq + e : lq + 4 * e);
-        const int pcol = 16 * (cb0 + c) + li;
-        const int row = 6 * (prow % kDnCams) + prow / kDnCams;
-        const int col = 6 * (pcol % kDnCams) + pcol / kDnCams;
-        out[row * kDnRows + col] = T(acc[r][c][e]);
-      }
+    for (int e = 0; e < 4; ++e) {
+      if (HC != kDnCams && wv + 4 * x > 8) break;
+      // LDS rows back to camera-major rows (6 per camera)
+      const int prow = 16 * tile_r(x) + (M::row_major_d ? 4 * lq + e : lq + 4 * e);
+      const int pcol = 16 * tile_c(x) + li;
+      const int row = 6 * (HC * qa + prow % HC) + prow / HC;
+      const int col = 6 * (HC * qb + pcol % HC) + pcol / HC;
+      out[row * kDnRows + col] = T(acc[x][e]);
+    }
 }
 
 // One camera row (6 rows) of one tile pair: the ranges' partial products summed in FP64
@@ -4503,20 +4611,23 @@ int prepare_kernels() {
     }
   }
   // the dense form's product kernel
-  const void *dense_kernels[4] = {(const void *)k_dense_schur<double, double>,
-                                  (const void *)k_dense_schur<float, float>,
-                                  (const void *)k_dense_schur<float, _Float16>,
-                                  (const void *)k_dense_schur<float, bf16s>};
-  const size_t dense_lds[4] = {dn_lds_bytes<double, double>(), dn_lds_bytes<float, float>(),
-                               dn_lds_bytes<float, _Float16>(), dn_lds_bytes<float, bf16s>()};
   g_dense_ok = true;
-  for (int p = 0; p < 4; ++p)
-    if (dense_lds[p] + 4096 > (size_t)lim ||
-        hipFuncSetAttribute(dense_kernels[p], hipFuncAttributeMaxDynamicSharedMemorySize, (int)dense_lds[p]) !=
-            hipSuccess) {
+  auto allow_dense = [&](const void *f, size_t bytes) {
+    if (bytes + 4096 > (size_t)lim ||
+        hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) {
       (void)hipGetLastError();
       g_dense_ok = false;
     }
+  };
+  allow_dense((const void *)k_dense_schur<double, double, kDnCams>, dn_lds_bytes<double, double>());
+  allow_dense((const void *)k_dense_schur<float, float, kDnCams>, dn_lds_bytes<float, float>());
+  allow_dense((const void *)k_dense_schur<float, _Float16, kDnCams>, dn_lds_bytes<float, _Float16>());
+  allow_dense((const void *)k_dense_schur<float, bf16s, kDnCams>, dn_lds_bytes<float, bf16s>());
+  constexpr int kHalf = kDnCams / 2;
+  allow_dense((const void *)k_dense_schur<double, double, kHalf>, dn_lds_bytes<double, double, kHalf>());
+  allow_dense((const void *)k_dense_schur<float, float, kHalf>, dn_lds_bytes<float, float, kHalf>());
+  allow_dense((const void *)k_dense_schur<float, _Float16, kHalf>, dn_lds_bytes<float, _Float16, kHalf>());
+  allow_dense((const void *)k_dense_schur<float, bf16s, kHalf>, dn_lds_bytes<float, bf16s, kHalf>());
   done = true;
   return 0;
 }
@@ -4657,7 +4768,11 @@ static hipError_t lm_iteration(const BatchPlan &bp, int pcg_max, int max_tcols, 
   }
   if (bp.n_dsy) {
     Timed t(tm, K_DENSE_SCHUR, s);
-    k_dense_schur<T, S><<<bp.n_dsy, 256, dn_lds_bytes<T, S>(), s>>>(bp.probs, bp.dsy);
+    k_dense_schur<T, S, kDnCams><<<bp.n_dsy, 256, dn_lds_bytes<T, S>(), s>>>(bp.probs, bp.dsy);
+  }
+  if (bp.n_dsq) {
+    Timed t(tm, K_DENSE_SCHUR, s);
+    k_dense_schur<T, S, kDnCams / 2><<<bp.n_dsq, 256, dn_lds_bytes<T, S, kDnCams / 2>(), s>>>(bp.probs, bp.dsq);
   }
   if (bp.n_dre) {
     Timed t(tm, K_DENSE_REDUCE, s);

@@ -145,7 +145,7 @@ struct DevProblem {
 struct Batch {
   std::vector<ProbDev> probs;
   std::vector<int> tags;
-  std::vector<Tile> tiles[18];  // pt, diag, off, pcg, cam, ctl, pp, ch, red, fin, fsh, pri, dpt, dcm, dsy, dre, pcs, pcb
+  std::vector<Tile> tiles[19];  // pt, diag, off, pcg, cam, ctl, pp, ch, red, fin, fsh, pri, dpt, dcm, dsy, dre, pcs, pcb, dsq
   std::vector<char> host;
   void *dev = nullptr;
   size_t cap = 0;

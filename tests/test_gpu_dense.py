@@ -117,6 +117,49 @@ def test_dense_reduced_precision_final_rms(balib, prec):
     assert abs(rms - rms_ref) <= 1e-3
 
 
+_tile_refs = {}
+
+
+def _tile_ref(cams, pts):
+    """Arc scene without every fifth (camera, point) of a lattice, so that tiles hold points
+    that some of their cameras do not see, with the oracle's S and the largest entry of the
+    camera blocks of H."""
+    if (cams, pts) not in _tile_refs:
+        s = make_arc_scene(cams, pts, seed=400 + cams)
+        keep = (7 * s.obs_cam + 3 * s.obs_pt) % 5 != 0
+        s.obs_cam, s.obs_pt, s.obs_uv, s.outlier = (x[keep] for x in (s.obs_cam, s.obs_pt, s.obs_uv, s.outlier))
+        p = O.Problem.from_scene(s)
+        H, g, _, _, _ = O.normal_equations(p)
+        n = 6 * O._free_index(p.fixed)[1]
+        S = O.schur_blocks(H, g, O.damping_diag(H.diagonal()), 1e-4, n)[0]
+        _tile_refs[cams, pts] = s, S, np.abs(H[:n, :n]).max()
+    return _tile_refs[cams, pts]
+
+
+@pytest.mark.parametrize("prec,tol", [("f64", 1e-12), ("f32", 2e-5), ("f16j", 3.9e-3), ("bf16j", 3.1e-2)])
+@pytest.mark.parametrize("cams,pts", [(3, 31), (9, 33), (10, 300), (17, 513), (18, 600), (26, 257), (34, 1100),
+                                      (44, 6000)])
+def test_dense_reduced_system_at_tile_edges(balib, cams, pts, prec, tol):
+    """S of the first iteration where the product's tiles are cut: one free camera more or
+    fewer than 8, 16, 24 and 32, ranges of points that end inside a chunk, whole tile pairs
+    (44 cameras, 6000 points) and their quarters (the others).  Within tol of the oracle,
+    relative to the largest entry of the camera blocks of H, which bounds the sums of
+    absolute products: 16-bit 8 roundings of 2^-11 / 2^-8 (four stored Jacobian factors, two
+    operands, slack), FP32 and FP64 the bars of the element-wise tests."""
+    s, S, scale = _tile_ref(cams, pts)
+    _say("device iteration export:", s.n_cams, s.n_pts, s.n_obs, prec)
+    p = balib.Problem.from_scene(s, max_iters=1, precision=prec, flags=DENSE)
+    form = p.info()["schur_form"]
+    dev = p.debug_iteration()
+    p.close()
+    assert form == 2
+    nf = S.shape[0] // 6
+    Sd = dev["S"].reshape(nf, nf, 6, 6).transpose(0, 2, 1, 3).reshape(6 * nf, 6 * nf)
+    err = float(np.abs(Sd - S).max() / scale)
+    _say("S error", err)
+    assert err <= tol
+
+
 def test_dense_problems_in_a_served_mix(balib):
     """Dense-form problems among chunk-form ones in the server: each result equals,
     bit for bit, the same problem solved alone."""
