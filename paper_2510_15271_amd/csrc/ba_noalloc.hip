@@ -56,7 +56,7 @@ extern "C" int ba_pose_batch_noalloc(int32_t n_req, const ba_pose_request *reqs,
     rp[i] = &reqs[i];
   }
   PoseBatch pb;
-  pb.pack(rp, std::vector<const ba_options *>(n_req, opt));
+  if (int e = pb.pack(rp, std::vector<const ba_options *>(n_req, opt))) return e;
   if (pb.bytes() > (size_t)BA_POSE_NOALLOC_MAX_BYTES)
     return fail(BA_ENOMEM, "pose batch needs %zu bytes of staging, more than the %zu the no-allocation entry holds",
                 pb.bytes(), (size_t)BA_POSE_NOALLOC_MAX_BYTES);

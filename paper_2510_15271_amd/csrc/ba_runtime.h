@@ -6,6 +6,7 @@
 #include <cstdint>
 #include <string>
 #include <utility>
+#include <memory>
 #include <vector>
 
 #include "../../include/ba.h"
@@ -178,13 +179,20 @@ struct PoseBatch {
   int n = 0;
   int64_t n_corr = 0;
   std::vector<PoseDev> hdr;
-  std::vector<double> X;
-  std::vector<float> uv;
+  std::unique_ptr<double[]> X;  // [n_corr][3]
+  std::unique_ptr<float[]> uv;  // [n_corr][2]
   // opts[i]: the options of request i (its max_iters and huber_delta)
   int pack(const std::vector<const ba_pose_request *> &reqs, const std::vector<const ba_options *> &opts);
   size_t bytes() const;
   // Upload, launch and queue the download of the headers into hdr (caller syncs).
   int run(char *base, hipStream_t s, KernelTimer *tm);
+  // The parts of pack and run: headers and staging arrays, the correspondences of the
+  // requests [i0, i1) (false: one of them is not finite), and what follows their upload.
+  int lay_out(const std::vector<const ba_pose_request *> &reqs, const std::vector<const ba_options *> &opts);
+  bool pack_range(const std::vector<const ba_pose_request *> &reqs, int i0, int i1);
+  double *dev_X(char *base) const;
+  float *dev_uv(char *base) const;
+  int launch(char *base, hipStream_t s, KernelTimer *tm);
 };
 // A count of the CUs that one-launch PCG runs may occupy at once on a device, so that the
 // workgroups of two of them never wait for each other's CUs: a solve (or a server) takes

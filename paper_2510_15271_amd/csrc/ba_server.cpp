@@ -497,8 +497,8 @@ void ba_server::loop() {
         rp.push_back(&r->preq);
         ro.push_back(&r->opt);
       }
-      pb.pack(rp, ro);
-      if (pb_ok && pb.run((char *)mem + pb_off, stream, nullptr) != BA_OK) fatal = BA_EDEVICE;
+      if (pb.pack(rp, ro) != BA_OK) fatal = BA_ENOMEM;
+      if (pb_ok && fatal == BA_OK && pb.run((char *)mem + pb_off, stream, nullptr) != BA_OK) fatal = BA_EDEVICE;
       // the headers' download goes to pageable memory: wait for it
       if (hipStreamSynchronize(stream) != hipSuccess) fatal = BA_EDEVICE;
       if (pb_ok) {

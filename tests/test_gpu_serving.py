@@ -163,6 +163,28 @@ def test_pose_requests_through_server_equal_batch(balib):
     assert st["done"] == len(reqs)
 
 
+@pytest.mark.parametrize("n", [15, 16, 1200])
+def test_pose_batch_in_blocks_equals_single_requests(balib, n):
+    """A call's requests are packed and uploaded in blocks of 65536 correspondences: each
+    result equals, bit for bit, the request alone, and of two requests with a value that is
+    not finite, in different blocks, the first is the one that is refused."""
+    reqs = make_config4_requests(n, seed=1006)
+    tot = np.cumsum([len(q.X) for q in reqs])
+    _say("correspondences", tot[-1])
+    res = balib.pose_batch(reqs, iters=10, huber_delta=1.0)
+    edge = [int(i) for i in np.searchsorted(tot, np.arange(65536, tot[-1], 65536))]  # around the cuts
+    for i in sorted({0, 1, n // 2, n - 2, n - 1, *edge, *(e + 1 for e in edge if e + 1 < n)}):
+        one = balib.pose_batch([reqs[i]], iters=10, huber_delta=1.0)
+        assert np.array_equal(one["q"][0], res["q"][i]) and np.array_equal(one["t"][0], res["t"][i]), i
+        assert one["cost"][0] == res["cost"][i] and one["status"][0] == res["status"][i]
+    for i, v in ((n - 1, np.nan), (n // 2, np.inf)):
+        reqs[i].uv = reqs[i].uv.copy()
+        reqs[i].uv[-1, 1] = v
+    with pytest.raises(balib.BAError) as e:
+        balib.pose_batch(reqs, iters=10, huber_delta=1.0)
+    assert e.value.code == balib.BA_EINVAL and f"request {n // 2}:" in str(e.value) and "pixel" in str(e.value)
+
+
 def test_pose_requests_with_different_options_keep_their_own(balib):
     """Pose requests admitted in one scheduler step but asking for different
     iteration counts and Huber thresholds: each result equals, bit for bit,
