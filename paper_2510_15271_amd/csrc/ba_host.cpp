@@ -1182,6 +1182,22 @@ void Batch::clear() {
   for (auto &v : tiles) v.clear();
 }
 
+// Workgroups are dealt to the 8 XCDs round-robin (workgroup j to XCD j mod 8),
+// and each XCD has its own L2.  Reordering a tile list so that XCD x receives a
+// contiguous run of tiles keeps the blocks that share a camera's records on one
+// L2.  The map is a bijection and changes no result.
+static void xcd_contiguous(std::vector<Tile> &v) {
+  constexpr int kXcd = 8;
+  const size_t n = v.size();
+  if (n < 2 * kXcd) return;
+  size_t start[kXcd + 1];
+  start[0] = 0;
+  for (int x = 0; x < kXcd; ++x) start[x + 1] = start[x] + n / kXcd + ((size_t)x < n % kXcd ? 1 : 0);
+  std::vector<Tile> out(n);
+  for (size_t j = 0; j < n; ++j) out[j] = v[start[j % kXcd] + j / kXcd];
+  v.swap(out);
+}
+
 void Batch::add(const ProbDev &pd, int slot_tag) {
   const int pi = (int)probs.size();
   probs.push_back(pd);
@@ -1189,12 +1205,26 @@ void Batch::add(const ProbDev &pd, int slot_tag) {
   for (int t = 0; t < pd.n_pt_tiles; ++t) tiles[0].push_back(Tile{pi, t});
   if (pd.dense) {
     for (int t = 0; t < pd.n_pt_tiles; ++t) tiles[12].push_back(Tile{pi, t});
-    for (int a = 0; a < pd.Cf; ++a) tiles[13].push_back(Tile{pi, a});
+    // Per problem, so that each spreads over all XCDs (over the whole batch, the XCDs of the
+    // largest problems end last: 512-problem FP32 stream 2.35 s, so 1.89).  Camera sums:
+    // neighbouring cameras' records of a point share cache lines (196 free cameras x 20011
+    // points, 16-bit records: k_dense_cams 124 us instead of 145); products: by range, so
+    // that an XCD's workgroups share the records.
+    auto per_xcd = [&](std::vector<Tile> &list, std::vector<Tile> &own) {
+      xcd_contiguous(own);
+      list.insert(list.end(), own.begin(), own.end());
+    };
+    std::vector<Tile> own;
+    for (int a = 0; a < pd.Cf; ++a) own.push_back(Tile{pi, a});
+    per_xcd(tiles[13], own);
     if (pd.dn_quarter)
       for (int t = 0; t < 4 * pd.dn_pairs * pd.dn_split; ++t) tiles[18].push_back(Tile{pi, t});
-    else
-      for (int r = 0; r < pd.dn_split; ++r)  // by range: an XCD's workgroups share the records
-        for (int t = 0; t < pd.dn_pairs; ++t) tiles[14].push_back(Tile{pi, t * pd.dn_split + r});
+    else {
+      own.clear();
+      for (int r = 0; r < pd.dn_split; ++r)
+        for (int t = 0; t < pd.dn_pairs; ++t) own.push_back(Tile{pi, t * pd.dn_split + r});
+      per_xcd(tiles[14], own);
+    }
     for (int t = 0; t < pd.dn_pairs * kDnCams; ++t) tiles[15].push_back(Tile{pi, t});
     for (int t = 0; t < pd.n_fsh_tiles; ++t) tiles[10].push_back(Tile{pi, t});
   } else if (pd.chunked) {
@@ -1216,29 +1246,9 @@ void Batch::add(const ProbDev &pd, int slot_tag) {
   for (int t = 0; t < pd.n_pri_tiles; ++t) tiles[11].push_back(Tile{pi, t});
 }
 
-// Workgroups are dealt to the 8 XCDs round-robin (workgroup j to XCD j mod 8),
-// and each XCD has its own L2.  Reordering a tile list so that XCD x receives a
-// contiguous run of tiles keeps the blocks that share a camera's records on one
-// L2.  The map is a bijection and changes no result.
-static void xcd_contiguous(std::vector<Tile> &v) {
-  constexpr int kXcd = 8;
-  const size_t n = v.size();
-  if (n < 2 * kXcd) return;
-  size_t start[kXcd + 1];
-  start[0] = 0;
-  for (int x = 0; x < kXcd; ++x) start[x + 1] = start[x] + n / kXcd + ((size_t)x < n % kXcd ? 1 : 0);
-  std::vector<Tile> out(n);
-  for (size_t j = 0; j < n; ++j) out[j] = v[start[j % kXcd] + j / kXcd];
-  v.swap(out);
-}
-
 int Batch::upload(hipStream_t s) {
   xcd_contiguous(tiles[2]);
   xcd_contiguous(tiles[7]);
-  // camera sums of the dense form: neighbouring cameras' records of a point share cache
-  // lines (197 cameras x 20011 points, 16-bit records: k_dense_cams 124 us instead of 145)
-  xcd_contiguous(tiles[13]);
-  xcd_contiguous(tiles[14]);
   size_t need = probs.size() * sizeof(ProbDev);
   constexpr int NL = 19;
   size_t offs[NL];
