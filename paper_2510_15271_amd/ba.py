@@ -438,7 +438,7 @@ class Problem:
         return self
 
     def set_barrier_polls(self, polls):
-        """Poll bound of the resident PCG's grid barrier (a test hook; 0 makes it give up at once)."""
+        """Poll bound of the one-launch PCG's waits (a test hook; 0 makes them give up at once)."""
         _check(lib().ba_set_barrier_polls(self._h, int(polls)))
         return self
 

@@ -86,9 +86,9 @@ struct LMState {
   int32_t iter, max_iters, relin, status;
   int32_t accepted, cur, pcg_done, pcg_iters;
   int32_t pcg_max, init_done, n_masked;
-  int32_t pcg_fault;       // 1: the resident PCG's grid barrier timed out (the solve stops)
-  int32_t halted;          // 1: the solve ended before max_iters (after a barrier time-out)
-  int32_t bar_polls;       // polls after which the resident PCG's grid barrier gives up
+  int32_t pcg_fault;       // 1: a wait of the one-launch PCG timed out (the solve stops)
+  int32_t halted;          // 1: the solve ended before max_iters (after such a time-out)
+  int32_t bar_polls;       // polls after which a wait of the one-launch PCG gives up
 };
 // Default of LMState::bar_polls: about a second of polling.
 constexpr int32_t kBarPollsDefault = 1 << 20;
@@ -128,7 +128,7 @@ struct ProbDev {
   int32_t n_pt_tiles, n_pcg_tiles, n_cam_tiles;
   int32_t max_tcols;     // longest tile column list
   int32_t pcg_rows;      // rows per PCG tile: kPcgRows, kPcgRowsSparse or kPcgRowsMax
-  int32_t pcg_resident;  // 1: the whole PCG runs in one launch with grid barriers (k_cg_run); 2: launched cooperatively
+  int32_t pcg_resident;  // 1: one launch was asked for by flag (k_cg_run, k_cg_small); 2: launched cooperatively
   int32_t pcg_small;     // 1: the whole PCG by one workgroup (k_cg_small)
   int32_t chunked;       // 1: point-chunk Schur form, 0: pair-list form
   int32_t n_ch;          // point chunks (chunk form)
@@ -333,7 +333,7 @@ bool dense_form_available();
 // Whether the PCG runs in its one-reduction form (one launch per iteration) for
 // a plan whose longest tile column list is max_tcols.
 bool one_reduction_pcg(int precision, int max_tcols);
-// True when the resident PCG (one launch, grid barriers) can run a problem: every
+// True when the PCG in one launch that does not fall back can run a problem: every
 // tile's columns fit one sweep and all n_tiles workgroups can be resident at once.
 bool resident_pcg_fits(int precision, int rows, int n_tiles, int max_tcols);
 // Whether one workgroup runs the PCG of a problem of Cf free cameras in 4-row tiles.

@@ -14,10 +14,11 @@
 //   schur_off    one wavefront per upper block S_ab: sum over the points seen
 //                by a and b of -Y_aj W_bj^T from precomputed pair lists, one
 //                wave reduction, written to S_ab and its transpose.
-//   cg_start /   block-Jacobi PCG in its one-reduction form, one launch per
-//   cg_step      iteration: block-sparse S u over the columns a tile reads,
-//                FP64 dot products from per-tile partials reduced in a fixed
-//                order by every consumer -- no grid barrier, no float atomics.
+//   cg_start /   block-Jacobi PCG in its one-reduction form: block-sparse S u over
+//   cg_run /     the columns a tile reads, FP64 dot products from per-tile
+//   cg_small /   partials reduced in a fixed order by every consumer, no float
+//   cg_step      atomics.  One launch per linear solve (run: tiles exchange
+//                stamped words; small: one workgroup), or one per iteration.
 //                (pcg_spmv / pcg_update: the textbook form, two launches per
 //                iteration, for systems whose tile columns exceed LDS.)
 //   cam_update   T <- Exp(dc) T, camera part of the predicted decrease.
@@ -1572,8 +1573,8 @@ __global__ __launch_bounds__(chunk_threads<T>()) void k_schur_chunk(const ProbDe
 // hold an element each and a block is two store instructions (56 lane permutes and eight
 // partial stores before).  Where blocks have few rows the wave's chain of loads, exchange
 // and stores bounds it: a pose graph of 1500 frames 23 -> 12 us, a vehicle rig of 200
-// frames 30 -> 17; with 16 rows per block (1.2M points, 513 MB) the reads: 217 us before
-// and after, and no less with workgroups that load the next block ahead (215 to 262).
+// frames 30 -> 17; with many rows per block (1.2M points, 1.03 GB) the reads: 217 us before
+// and after, 4.7 TB/s, and no less with workgroups that load the next block ahead (215 to 262).
 template <class T>
 __global__ __launch_bounds__(256) void k_schur_reduce(const ProbDev *__restrict__ probs,
                                                       const Tile *__restrict__ tiles) {
