@@ -69,6 +69,20 @@ def test_rig_f64_one_extrinsic_fixed_no_priors(balib):
     assert np.max(np.abs(O.quat_to_rot(res["qe"][0]) - O.quat_to_rot(s.qe0[0]))) <= 1e-14
 
 
+@pytest.mark.parametrize("n_rig", [2, 4, 5])
+def test_rig_f64_extrinsics_in_and_out_of_registers(balib, n_rig):
+    """Rigs of two, four and five cameras (the projection holds the adjoints of the first
+    three in registers): every C_n of 6 FP64 iterations within 1e-9 of the oracle."""
+    s = make_rig_drive(10, 260, n_rig=n_rig, seed=30 + n_rig)
+    pairs = np.array([[0, k] for k in range(1, n_rig)])
+    ref = O.lm_rig(_oracle(s, prior_ext=10.0, rig_pairs=pairs, prior_rig=10.0), O.LMOptions(max_iters=6))
+    res, _ = _solve(balib, s, prior_ext=10.0, prior_rig=10.0, rig_pairs=pairs, max_iters=6, pcg_max_iters=400,
+                    pcg_rel_tol=1e-14, precision="f64")
+    rel = np.abs(res["iter_cost"] - np.array(ref.iter_cost)) / np.array(ref.iter_cost)
+    _say("max rel cost diff", rel.max(), ref.accepted)
+    assert rel.max() <= 1e-9
+
+
 def test_rig_f32_drive_cost_matches_oracle_at_device_state(balib):
     """200 frames of the 3-camera rig (the benchmark's rig workload), FP32, 10 LM
     iterations, PCG 50 / 1e-6: the device's cost equals the oracle's rig cost at the
