@@ -322,6 +322,18 @@ int ba_set_profiling(ba_problem *p, int32_t mask, int32_t stride);
    one workgroup run every linear solve.  Applies from the next solve on; BA_EINVAL for
    polls < 0. */
 int ba_set_barrier_polls(ba_problem *p, int32_t polls);
+/* How the linear solves of p's solves are launched, from the next solve on: BA_PCG_AUTO (the
+   default) as described at BA_FLAG_PCG_RESIDENT, BA_PCG_PER_LAUNCH one launch per PCG
+   iteration, whatever the flags and the problem's size: for a program whose other work
+   keeps the device's CUs busy for long, and the form the others are tested against.  The
+   iterates are the same, bit for bit.  BA_EINVAL for another value. */
+#define BA_PCG_AUTO 0
+#define BA_PCG_PER_LAUNCH 1
+int ba_set_pcg_form(ba_problem *p, int32_t form);
+/* The form the last solve of p took: BA_PCG_AUTO if one launch ran each linear solve,
+   BA_PCG_PER_LAUNCH if each PCG iteration was a launch.  BA_ESTATE while a solve is in
+   flight and before the first. */
+int ba_get_pcg_form(const ba_problem *p, int32_t *form);
 /* Test export of one LM iteration's intermediate quantities, for element-wise
    checks of the linearisation, the Schur complement (paper Sec. 4.3; the reduced
    camera system of the method), the PCG solution and the back-substitution.  Runs one

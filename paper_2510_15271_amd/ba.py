@@ -160,6 +160,8 @@ def lib():
     L.ba_destroy.restype = None
     L.ba_set_profiling.argtypes = [vp, i32, i32]
     L.ba_set_barrier_polls.argtypes = [vp, i32]
+    L.ba_set_pcg_form.argtypes = [vp, i32]
+    L.ba_get_pcg_form.argtypes = [vp, C.POINTER(i32)]
     L.ba_debug_iteration_export.argtypes = [vp, C.POINTER(DebugIteration)]
     L.ba_get_kernel_times.argtypes = [vp, i32, C.POINTER(C.c_char_p), dp, C.POINTER(i32),
                                       C.POINTER(i32)]
@@ -190,6 +192,7 @@ FLAG_PCG_WIDE = 8
 FLAG_PCG_RESIDENT = 16
 FLAG_DENSE_SCHUR = 32
 FLAG_PCG_COOPERATIVE = 64
+PCG_AUTO, PCG_PER_LAUNCH = 0, 1
 
 
 def options(max_iters=10, pcg_max_iters=50, pcg_rel_tol=1e-6, lambda0=1e-4, huber_delta=0.0,
@@ -441,6 +444,17 @@ class Problem:
         """Poll bound of the one-launch PCG's waits (a test hook; 0 makes them give up at once)."""
         _check(lib().ba_set_barrier_polls(self._h, int(polls)))
         return self
+
+    def set_pcg_form(self, form):
+        """PCG_AUTO, or PCG_PER_LAUNCH: one launch per PCG iteration from the next solve on."""
+        _check(lib().ba_set_pcg_form(self._h, int(form)))
+        return self
+
+    def pcg_form(self):
+        """The form the last solve took: PCG_AUTO if one launch ran each linear solve."""
+        f = C.c_int32()
+        _check(lib().ba_get_pcg_form(self._h, C.byref(f)))
+        return f.value
 
     def debug_iteration(self):
         """ba_debug_iteration_export: one LM iteration from the current state and its

@@ -1407,8 +1407,11 @@ struct ba_problem {
   bool solved = false;
   bool profiling = false;
   bool use_graph = true;
+  bool pcg_steps = false;  // BA_PCG_PER_LAUNCH
+  bool one = false;        // the last solve ran its linear solves in one launch each
   // the launch sequence of one solve, captured once: with the PCG as this problem runs it,
-  // and launched per iteration, for when the one-launch run's CUs are taken
+  // and launched per iteration, for when that was asked for or the one-launch run's CUs are
+  // taken
   hipGraph_t graph[2] = {};
   hipGraphExec_t graph_exec[2] = {};
   int device = 0;  // the device the problem lives on
@@ -1971,7 +1974,7 @@ static int queue_solve(ba_problem *p, const bool one) {
     if (p->dp.max_iters > 0) e = hipGraphLaunch(p->seg_exec[0], p->stream);
     for (int it = 0; it < p->dp.max_iters && e == hipSuccess; ++it) {
       // (without BA_FLAG_PCG_RESIDENT a run counts its steps, also when one launch runs them)
-      p->timer.begin(K_PCG_CG, p->stream, p->batch.plan.single.pcg_resident ? 1 : p->dp.pcg_max);
+      p->timer.begin(K_PCG_CG, p->stream, one && p->batch.plan.single.pcg_resident ? 1 : p->dp.pcg_max);
       // the resident run is one kernel: launched directly, not as a one-node graph
       e = one ? launch_lm_iteration(p->dp.precision, p->batch.plan, p->dp.pcg_max, p->dp.max_tcols,
                                                    p->stream, nullptr, LM_PCG)
@@ -2011,9 +2014,12 @@ int ba_solve_async(ba_problem *p) {
   const int per_wg = flagged ? 1 : sy.pcg_run;
   // (one workgroup waits for no other)
   const int n = per_wg && !sy.pcg_small ? ((sy.Cf + sy.pcg_rows - 1) / sy.pcg_rows + per_wg - 1) / per_wg : 0;
-  const bool one = sy.pcg_small || (n > 0 && take_cus(p->device, n, flagged));
+  const bool one = !p->pcg_steps && (sy.pcg_small || (n > 0 && take_cus(p->device, n, flagged)));
   if (one) p->cus = n;
-  (p->rig ? p->rig->batch : p->batch).plan.pcg_run = one ? per_wg : 0;
+  p->one = one;
+  BatchPlan &plan = (p->rig ? p->rig->batch : p->batch).plan;
+  plan.pcg_run = one ? per_wg : 0;
+  plan.pcg_steps = one ? 0 : 1;
   const int rc = queue_solve(p, one);
   if (rc != BA_OK) {
     if (p->cus) (void)hipStreamSynchronize(p->stream);  // whatever was queued before the error
@@ -2368,6 +2374,22 @@ int ba_set_barrier_polls(ba_problem *p, int32_t polls) {
   return BA_OK;
 }
 
+int ba_set_pcg_form(ba_problem *p, int32_t form) {
+  if (!p) return fail(BA_EINVAL, "problem is NULL");
+  if (form != BA_PCG_AUTO && form != BA_PCG_PER_LAUNCH) return fail(BA_EINVAL, "unknown PCG form %d", form);
+  p->pcg_steps = form == BA_PCG_PER_LAUNCH;
+  return BA_OK;
+}
+
+int ba_get_pcg_form(const ba_problem *p, int32_t *form) {
+  if (!p || !form) return fail(BA_EINVAL, "NULL argument");
+  if (p->pending) return fail(BA_ESTATE, "a solve is in flight");
+  if (!p->solved) return fail(BA_ESTATE, "no solve has run since the last reset");
+  *form = p->one && one_reduction_pcg(p->dp.precision, p->rig ? p->rig->sy.max_tcols : p->dp.max_tcols)
+              ? BA_PCG_AUTO : BA_PCG_PER_LAUNCH;
+  return BA_OK;
+}
+
 int ba_debug_iteration_export(ba_problem *p, ba_debug_iteration *out) {
   if (!p || !out) return fail(BA_EINVAL, "NULL argument");
   if (p->rig) return fail(BA_EINVAL, "the iteration export covers single-view problems, not vehicle rigs");
@@ -2378,7 +2400,10 @@ int ba_debug_iteration_export(ba_problem *p, ba_debug_iteration *out) {
   dp.pending_state = dp.fresh_state();
   dp.pending_state.max_iters = 1;
   hipError_t e = hipMemcpyAsync(v.st, &dp.pending_state, sizeof(LMState), hipMemcpyHostToDevice, p->stream);
+  // a launch per PCG iteration: the same iterates, and no CUs to count
   p->batch.plan.pcg_run = 0;
+  p->batch.plan.pcg_steps = 1;
+  p->one = false;
   if (e == hipSuccess) e = launch_lm_iteration(dp.precision, p->batch.plan, dp.pcg_max, dp.max_tcols, p->stream, nullptr);
   if (e == hipSuccess) e = launch_eval(dp.precision, p->batch.plan, p->stream, nullptr);
   double *dev = nullptr;  // records widened to FP64: r (2), J_c (12), J_p (6) per observation

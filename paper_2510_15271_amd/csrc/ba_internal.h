@@ -282,6 +282,8 @@ struct BatchPlan {
   int32_t n_probs;
   int32_t pcg_rows;  // rows per PCG tile shared by every problem of the batch, 0 if mixed
   int32_t big_rows;  // ... by those whose PCG takes more than one workgroup
+  int32_t pcg_steps; // 1: a launch per PCG iteration for every problem, also where one workgroup
+                     // or the flag's resident run would do (ba_set_pcg_form)
   int32_t pcg_run;   // the PCG in one launch that falls back to one workgroup when its tiles
                      // cannot all run at once: tiles per workgroup, 0: a launch per iteration
   ProbDev single;  // host copy of the descriptor when n_probs == 1 (passed by value to short kernels)

@@ -4723,14 +4723,15 @@ int falling_back_pcg(int precision, int rows, int n_tiles, int max_tcols) {
 // one launch per iteration.
 template <class T>
 static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hipStream_t s, KernelTimer *tm) {
-  const bool lone = bp.n_probs == 1, flagged = lone && bp.single.pcg_resident && bp.single.rig_mode == 0;
-  const int per_wg = flagged ? 1 : bp.pcg_run;
+  const bool lone = bp.n_probs == 1;
+  const bool flagged = lone && bp.single.pcg_resident && bp.single.rig_mode == 0 && !bp.pcg_steps;
+  const int per_wg = flagged ? 1 : bp.pcg_steps ? 0 : bp.pcg_run;
   int fall_back = flagged ? 0 : 1;
   // one event pair around the whole run: per-launch events would add their own
   // overhead to launches this short; a run counts its steps, and one where it was asked
   // for as one launch
   Timed t(tm, K_PCG_CG, s, flagged ? 1 : pcg_max);
-  if (bp.n_pcs) {  // the problems that one workgroup solves
+  if (bp.n_pcs && !bp.pcg_steps) {  // the problems that one workgroup solves
     void *args1[] = {(void *)&bp.single, (void *)&bp.probs, (void *)&pcg_max, (void *)&fall_back};
     void *argsn[] = {(void *)&bp.probs, (void *)&bp.pcs, (void *)&pcg_max};
     const unsigned lds = 6 * cg_small_cams<T>() * sizeof(T);  // for cg_solo
@@ -4739,7 +4740,10 @@ static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hi
              : hipLaunchKernel((const void *)k_cg_small_batch<T>, dim3(bp.n_pcs), dim3(kCgThreads), argsn, lds, s);
     if (le != hipSuccess) return le;
   }
-  if (bp.n_pcb == 0) return hipSuccess;
+  // the tiles of the others
+  const Tile *tiles = bp.pcg_steps ? bp.pcg : bp.pcb;
+  const int n_tiles = bp.pcg_steps ? bp.n_pcg : bp.n_pcb;
+  if (n_tiles == 0) return hipSuccess;
   hipError_t le = hipSuccess;
   if (per_wg) {
     const unsigned lds = (unsigned)cg_run_lds_bytes(max_tcols, sizeof(T), per_wg);
@@ -4758,11 +4762,12 @@ static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hi
                                                   : hipLaunchKernel(f, grid, dim3(kCgThreads), args, lds, s);
   }
   const size_t ubytes = 6 * (size_t)max_tcols * sizeof(T);
-  const void *f = lone ? CgStep<T>::single(bp.big_rows) : CgStep<T>::multi(bp.big_rows);
+  const int rows = bp.pcg_steps ? bp.pcg_rows : bp.big_rows;
+  const void *f = lone ? CgStep<T>::single(rows) : CgStep<T>::multi(rows);
   for (int it = 0; it < pcg_max && le == hipSuccess; ++it) {
     void *args1[] = {(void *)&bp.single, (void *)&it};
-    void *argsn[] = {(void *)&bp.probs, (void *)&bp.pcb, (void *)&it};
-    le = hipLaunchKernel(f, dim3(bp.n_pcb), dim3(kCgThreads), lone ? args1 : argsn, ubytes, s);
+    void *argsn[] = {(void *)&bp.probs, (void *)&tiles, (void *)&it};
+    le = hipLaunchKernel(f, dim3(n_tiles), dim3(kCgThreads), lone ? args1 : argsn, ubytes, s);
   }
   return le;
 }
