@@ -103,7 +103,7 @@ REFINE_ROUNDS = 2
 REFINE_ITERS = 30  # LM iterations per round
 
 
-def refine_leg(ba, precision: str, n_pts: int, flags: int = 0, reps: int = 3) -> dict:
+def refine_leg(ba, precision: str, n_pts: int, flags: int = 0, reps: int = 3, pcg_form: int = 0) -> dict:
     """The two-stage iterative refinement (each round: 30 LM iterations, then
     culling with midpoint re-triangulation) on the same drive with 5 % of the
     pixels replaced by uniform outliers.  Whole-call wall time over `reps` runs
@@ -114,7 +114,7 @@ def refine_leg(ba, precision: str, n_pts: int, flags: int = 0, reps: int = 3) ->
     print("bench: generating the outlier drive", flush=True, file=sys.stderr)
     s = make_config1(n_pts=n_pts, outlier_frac=0.05, huber_delta=1.0)
     p = ba.Problem.from_scene(s, max_iters=REFINE_ITERS, pcg_max_iters=50, pcg_rel_tol=1e-6,
-                              precision=precision, flags=flags)
+                              precision=precision, flags=flags).set_pcg_form(pcg_form)
     info = p.info()
     p.refine(REFINE_STAGES, REFINE_ROUNDS)  # warm-up (graph capture)
     walls = []
@@ -609,6 +609,8 @@ def main():
                                        (0 if args.per_launch_pcg else ba.FLAG_PCG_RESIDENT),
                                  prior_abs=args.prior_abs, prior_seq=args.prior_seq,
                                  prior_seq_k=args.prior_seq_k)
+    pcg_form = ba.PCG_PER_LAUNCH if args.per_launch_pcg else ba.PCG_AUTO
+    prob.set_pcg_form(pcg_form)
     info = prob.info()
     names = list(prob.kernel_times().keys())
 
@@ -728,8 +730,9 @@ def main():
                    "pose_priors": ({"abs": args.prior_abs, "seq": args.prior_seq, "seq_k": args.prior_seq_k}
                                    if args.prior_abs > 0 or args.prior_seq > 0 else None),
                    "graph": not args.no_graph,
-                   "pcg": "resident (one launch per linear solve)" if info["pcg_resident"]
-                          else "one launch per iteration"},
+                   "pcg": "one launch per iteration" if prob.pcg_form() == ba.PCG_PER_LAUNCH
+                          else "resident (one launch per linear solve)" if info["pcg_resident"]
+                          else "one launch per linear solve"},
         "obs_per_s": round(info["n_obs"] * lm_per_s, 1),
         "device_ms_per_step": round(sum(dev_ms) / len(dev_ms), 3),
         "final_rms_px": r["rms_px"],
@@ -757,7 +760,7 @@ def main():
     if not args.no_refine and args.workload == "drive":
         out["refine"] = refine_leg(ba, args.precision, args.points or 250_000,
                                    (ba.FLAG_NO_GRAPH if args.no_graph else 0) |
-                                   (0 if args.per_launch_pcg else ba.FLAG_PCG_RESIDENT))
+                                   (0 if args.per_launch_pcg else ba.FLAG_PCG_RESIDENT), pcg_form=pcg_form)
     if not args.no_rig and args.workload == "drive":
         out["rig"] = rig_leg(ba, args.precision, ba.FLAG_NO_GRAPH if args.no_graph else 0)
     if not args.no_pose_graph and args.workload == "drive":
