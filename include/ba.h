@@ -62,7 +62,8 @@ extern "C" {
 #define BA_STATUS_NUMERICAL 2  /* the cost became non-finite                  */
 #define BA_STATUS_PCG_SYNC 3   /* a wait of the resident PCG timed out (its workgroups
                                   were not all resident at once): the solve stopped with the
-                                  step rejected; solve without BA_FLAG_PCG_RESIDENT         */
+                                  step rejected; solve without BA_FLAG_PCG_RESIDENT, where
+                                  such a wait falls back instead                            */
 
 typedef struct { double fx, fy, cx, cy; } ba_intrinsics;         /* pinhole, no distortion  */
 typedef struct { double qw, qx, qy, qz, tx, ty, tz; } ba_pose;   /* world -> camera         */
@@ -317,11 +318,14 @@ int ba_set_profiling(ba_problem *p, int32_t mask, int32_t stride);
    workgroups' values after which a wait gives up (default 1048576, about a second).  With
    BA_FLAG_PCG_RESIDENT and 0 every wait gives up at once, so every workgroup of the launch
    exits at its first wait, the LM iteration rejects its step, and the solve ends with
-   status BA_STATUS_PCG_SYNC and iters = that iteration's number.  Without the flag the
-   bound applies to the first wait of each linear solve (at most about 15 ms), and 0 makes
-   one workgroup run every linear solve.  Applies from the next solve on; BA_EINVAL for
-   polls < 0. */
+   status BA_STATUS_PCG_SYNC and iters = that iteration's number.  Without the flag a
+   wait that gives up (the first of a linear solve after at most about 15 ms) makes one
+   workgroup run the linear solve instead, and with 0 every linear solve.  Applies from the
+   next solve on; BA_EINVAL for polls < 0. */
 int ba_set_barrier_polls(ba_problem *p, int32_t polls);
+/* The same for the waits from PCG iteration first_iteration (>= 1, the first wait) on; those
+   before keep the default bound. */
+int ba_set_barrier_polls_from(ba_problem *p, int32_t polls, int32_t first_iteration);
 /* How the linear solves of p's solves are launched, from the next solve on: BA_PCG_AUTO (the
    default) as described at BA_FLAG_PCG_RESIDENT, BA_PCG_PER_LAUNCH one launch per PCG
    iteration, whatever the flags and the problem's size: for a program whose other work

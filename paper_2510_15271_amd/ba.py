@@ -160,6 +160,7 @@ def lib():
     L.ba_destroy.restype = None
     L.ba_set_profiling.argtypes = [vp, i32, i32]
     L.ba_set_barrier_polls.argtypes = [vp, i32]
+    L.ba_set_barrier_polls_from.argtypes = [vp, i32, i32]
     L.ba_set_pcg_form.argtypes = [vp, i32]
     L.ba_get_pcg_form.argtypes = [vp, C.POINTER(i32)]
     L.ba_debug_iteration_export.argtypes = [vp, C.POINTER(DebugIteration)]
@@ -440,9 +441,10 @@ class Problem:
         _check(lib().ba_set_profiling(self._h, m, int(stride)))
         return self
 
-    def set_barrier_polls(self, polls):
-        """Poll bound of the one-launch PCG's waits (a test hook; 0 makes them give up at once)."""
-        _check(lib().ba_set_barrier_polls(self._h, int(polls)))
+    def set_barrier_polls(self, polls, first_iteration=1):
+        """Poll bound of the one-launch PCG's waits from PCG iteration first_iteration on (a test
+        hook; 0 makes them give up at once)."""
+        _check(lib().ba_set_barrier_polls_from(self._h, int(polls), int(first_iteration)))
         return self
 
     def set_pcg_form(self, form):

@@ -1172,6 +1172,7 @@ LMState DevProblem::fresh_state() const {
   st.pcg_max = pcg_max;
   st.init_done = 0;
   st.bar_polls = bar_polls;
+  st.bar_from = bar_from;
   return st;
 }
 
@@ -2367,12 +2368,16 @@ int ba_set_profiling(ba_problem *p, int32_t mask, int32_t stride) {
   return BA_OK;
 }
 
-int ba_set_barrier_polls(ba_problem *p, int32_t polls) {
+int ba_set_barrier_polls_from(ba_problem *p, int32_t polls, int32_t first_iteration) {
   if (!p) return fail(BA_EINVAL, "problem is NULL");
   if (polls < 0) return fail(BA_EINVAL, "polls must be >= 0");
+  if (first_iteration < 1) return fail(BA_EINVAL, "first_iteration must be >= 1");
   p->dp.bar_polls = polls;
+  p->dp.bar_from = first_iteration;
   return BA_OK;
 }
+
+int ba_set_barrier_polls(ba_problem *p, int32_t polls) { return ba_set_barrier_polls_from(p, polls, 1); }
 
 int ba_set_pcg_form(ba_problem *p, int32_t form) {
   if (!p) return fail(BA_EINVAL, "problem is NULL");

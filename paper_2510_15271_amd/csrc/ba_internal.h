@@ -88,7 +88,8 @@ struct LMState {
   int32_t pcg_max, init_done, n_masked;
   int32_t pcg_fault;       // 1: a wait of the one-launch PCG timed out (the solve stops)
   int32_t halted;          // 1: the solve ended before max_iters (after such a time-out)
-  int32_t bar_polls;       // polls after which a wait of the one-launch PCG gives up
+  int32_t bar_polls;       // polls after which a wait of the one-launch PCG gives up ...
+  int32_t bar_from, pad;   // ... from this iteration of a linear solve on (kBarPollsDefault before)
 };
 // Default of LMState::bar_polls: about a second of polling.
 constexpr int32_t kBarPollsDefault = 1 << 20;

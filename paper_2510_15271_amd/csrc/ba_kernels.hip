@@ -2434,10 +2434,12 @@ __device__ __forceinline__ T stamped_value(const uint64_t *v) {
 // 3.7 us; against a launch per iteration, the 203-camera submap went from 8.5 to 3.7 us, a
 // 24-camera window from 6.1 to 3.3, the 9000-node pose graph from 13.8 to 5.6 and the
 // 3000-camera loop from 25 (with the launches that find the solve converged) to 15.
-// Unless the caller asked for the run by flag, it falls back (fall_back): all tiles must
-// have published their first products within kCgGatherPolls polls; otherwise one word,
-// set by the first tile to give up or to finish, sends every tile out before it has
-// changed anything, and tile 0 runs the per-launch steps of all tiles by itself.
+// Unless the caller asked for the run by flag, it falls back (fall_back): where a wait runs
+// out (the first one, for all tiles to have published their first products, after
+// kCgGatherPolls polls), one word, set by the first tile to give up or to finish, sends every
+// tile out before it has changed anything, and tile 0 runs the per-launch steps of all tiles
+// by itself.  Where the word says that a tile has finished, that tile has read every word
+// that is still waited for, so the wait goes on.
 constexpr int kCgRunTiles = 320;                                  // tiles at most
 constexpr int kCgRunFew = 16;                                      // up to which polls do not get in each other's way
 constexpr int kCgWaveCols = 10;                                   // columns per wave and set
@@ -2527,7 +2529,7 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
   if (!s_flag[0]) return;
   n_iter = min(n_iter, st->pcg_max);
   const double tol = st->pcg_tol, bb = st->pcg_bb;
-  const int polls = fall_back ? min(st->bar_polls, kCgGatherPolls) : st->bar_polls;
+  const int polls = st->bar_polls, polls_from = st->bar_from;
   const auto dec = as_global(pd.cg_dec);
   // ---- per-solve constants and the state of the tile's columns and own rows
   const bool col_lane = lane < 6 * kCgWaveCols;
@@ -2612,14 +2614,18 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
       else __builtin_amdgcn_s_sleep(10);
       bool all = false;
       uint64_t xv[NS][W], pv[2];
-      bool lost = false;
+      bool lost = false, go = false;
+      int lim = it < polls_from ? kBarPollsDefault : polls;
+      if (fall_back && it == 1) lim = min(lim, kCgGatherPolls);
       for (int n = 0; !all && !lost; ++n) {
-        if (fall_back && n >= polls && it == 1) {
-          // not every tile is running: one word decides for the whole grid
+        if (n >= lim) {
+          if (!fall_back || go) break;
+          // one word decides for the whole grid
           lost = cg_decide(dec, kCgSolo) == kCgSolo;
           if (lost) break;
-        } else if (n >= (fall_back ? kBarPollsDefault : polls)) {
-          break;
+          go = true;  // some tile has finished: the words are on their way
+          n = 0;
+          lim = kBarPollsDefault;
         } else if (fall_back && (n & 255) == 255) {
           lost = cg_decision(dec) == kCgSolo;
         }
@@ -2805,7 +2811,7 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
       if (wg == 0) cg_solo<T, R>(dpd, n_iter);
       return;
     }
-  } else if (polls <= 0) {
+  } else if (polls <= 0 && polls_from <= 1) {
     ok = false;  // no wait may succeed, also where the cap leaves none to make
   }
 #pragma unroll
@@ -2876,7 +2882,7 @@ __device__ __forceinline__ void cg_small_body(const ProbDev &pd, const ProbDev *
   __syncthreads();
   if (!s_flag[0]) return;
   n_iter = min(n_iter, st->pcg_max);
-  if (st->bar_polls <= 0) {  // the test hook: as a run whose workgroups do not meet
+  if (st->bar_polls <= 0 && st->bar_from <= 1) {  // the test hook: as a run whose workgroups do not meet
     if (fall_back) {
       cg_solo<T, kPcgRows>(dpd, n_iter);
     } else if (t == 0) {

@@ -82,6 +82,32 @@ def test_one_launch_pcg_equals_a_launch_per_iteration(balib, prec, case):
         p.close()
 
 
+@pytest.mark.parametrize("prec", ["f64", "f32"])
+@pytest.mark.parametrize("case", ["41 cameras", "175 tiles", "graph 16 rows", "graph pairs", "rig"])
+def test_a_wait_that_runs_out_falls_back_at_any_iteration(balib, prec, case):
+    """Waits that give up at the first, second, a later and the last iteration that has one:
+    without the flag the solve is the launch-per-iteration one with its ordinary status;
+    with the flag it stops with BA_STATUS_PCG_SYNC where an iteration gets that far."""
+    p = _problem(balib, case, prec).set_pcg_form(balib.PCG_PER_LAUNCH)
+    ref = p.solve().result()
+    p.set_pcg_form(balib.PCG_AUTO)
+    last = KW["pcg_max_iters"] - 1
+    for it in (1, 2, 7, last):
+        _say("device solves:", case, prec, "waits give up from iteration", it)
+        _same(ref, p.set_barrier_polls(0, it).reset().solve().result())
+    p.close()
+    if case in ("rig", "graph pairs"):
+        return
+    p = _problem(balib, case, prec, RESIDENT)
+    for it in (1, 2, 7, last):
+        r = p.set_barrier_polls(0, it).reset().solve().result()
+        if ref["pcg_iters"][0] >= it:
+            assert r["status"] == balib.STATUS_PCG_SYNC and r["iters"] == 1 and r["accepted"] == 0
+        else:
+            assert max(ref["pcg_iters"]) >= it or r["status"] == ref["status"]
+    p.close()
+
+
 def test_early_stop_and_cap(balib):
     """A loose tolerance (a few iterations) and a cap of 1 and 3 iterations, for one
     workgroup and several: every form stops where the launch-per-iteration one does."""
