@@ -109,8 +109,9 @@ typedef struct {
    the compute units of its run out of a count the library keeps per device, so that
    several solves (or servers) at once stay within the device; one that finds them taken
    launches its PCG per iteration instead.  Where other work keeps a workgroup from
-   starting (for about 15 ms), one workgroup runs the linear solve alone, slowly.  All
-   three give the same iterates, bit for bit.
+   starting (for about 15 ms, once per solve), those that run share the steps of a launch
+   per iteration among them, and the next 16 solves of the problem are launched per
+   iteration.  All three give the same iterates, bit for bit.
    BA_FLAG_PCG_RESIDENT: run each linear solve of a single-problem solve as one launch in
    any case, without that fall-back.  Used when every workgroup of the solve fits on the
    device at once (at most one 1024-thread workgroup per CU for 4-row tiles) and a tile's
@@ -319,8 +320,9 @@ int ba_set_profiling(ba_problem *p, int32_t mask, int32_t stride);
    BA_FLAG_PCG_RESIDENT and 0 every wait gives up at once, so every workgroup of the launch
    exits at its first wait, the LM iteration rejects its step, and the solve ends with
    status BA_STATUS_PCG_SYNC and iters = that iteration's number.  Without the flag a
-   wait that gives up (the first of a linear solve after at most about 15 ms) makes one
-   workgroup run the linear solve instead, and with 0 every linear solve.  Applies from the
+   wait that gives up (the first of a linear solve after at most about 15 ms) makes the
+   workgroups share the steps; with 0 every linear solve falls back and one workgroup, the
+   first, runs all of them.  Applies from the
    next solve on; BA_EINVAL for polls < 0. */
 int ba_set_barrier_polls(ba_problem *p, int32_t polls);
 /* The same for the waits from PCG iteration first_iteration (>= 1, the first wait) on; those
@@ -330,14 +332,15 @@ int ba_set_barrier_polls_from(ba_problem *p, int32_t polls, int32_t first_iterat
    default) as described at BA_FLAG_PCG_RESIDENT, BA_PCG_PER_LAUNCH one launch per PCG
    iteration, whatever the flags and the problem's size: for a program whose other work
    keeps the device's CUs busy for long, and the form the others are tested against.  The
-   iterates are the same, bit for bit.  BA_EINVAL for another value. */
+   iterates are the same, bit for bit.  After a fall-back BA_PCG_AUTO also ends the time
+   until one launch is tried again.  BA_EINVAL for another value. */
 #define BA_PCG_AUTO 0
 #define BA_PCG_PER_LAUNCH 1
 int ba_set_pcg_form(ba_problem *p, int32_t form);
 /* The form the last solve of p took: BA_PCG_AUTO if one launch ran each linear solve,
-   BA_PCG_PER_LAUNCH if each PCG iteration was a launch.  BA_ESTATE while a solve is in
-   flight and before the first. */
-int ba_get_pcg_form(const ba_problem *p, int32_t *form);
+   BA_PCG_PER_LAUNCH if each PCG iteration was a launch; fell_back, if not NULL: how many of
+   its linear solves fell back.  BA_ESTATE while a solve is in flight and before the first. */
+int ba_get_pcg_form(const ba_problem *p, int32_t *form, int32_t *fell_back);
 /* Test export of one LM iteration's intermediate quantities, for element-wise
    checks of the linearisation, the Schur complement (paper Sec. 4.3; the reduced
    camera system of the method), the PCG solution and the back-substitution.  Runs one

@@ -162,7 +162,7 @@ def lib():
     L.ba_set_barrier_polls.argtypes = [vp, i32]
     L.ba_set_barrier_polls_from.argtypes = [vp, i32, i32]
     L.ba_set_pcg_form.argtypes = [vp, i32]
-    L.ba_get_pcg_form.argtypes = [vp, C.POINTER(i32)]
+    L.ba_get_pcg_form.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
     L.ba_debug_iteration_export.argtypes = [vp, C.POINTER(DebugIteration)]
     L.ba_get_kernel_times.argtypes = [vp, i32, C.POINTER(C.c_char_p), dp, C.POINTER(i32),
                                       C.POINTER(i32)]
@@ -455,8 +455,14 @@ class Problem:
     def pcg_form(self):
         """The form the last solve took: PCG_AUTO if one launch ran each linear solve."""
         f = C.c_int32()
-        _check(lib().ba_get_pcg_form(self._h, C.byref(f)))
+        _check(lib().ba_get_pcg_form(self._h, C.byref(f), None))
         return f.value
+
+    def pcg_fell_back(self):
+        """How many of the last solve's linear solves fell back from their one launch."""
+        f, n = C.c_int32(), C.c_int32()
+        _check(lib().ba_get_pcg_form(self._h, C.byref(f), C.byref(n)))
+        return n.value
 
     def debug_iteration(self):
         """ba_debug_iteration_export: one LM iteration from the current state and its

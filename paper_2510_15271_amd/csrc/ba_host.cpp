@@ -895,7 +895,7 @@ size_t DevProblem::plan(const Symbolic &sy, int precision, int max_iters, Offset
     o.cg_xw[b] = L.take(Cf * 6 * (T / 4) * 8);
     o.cg_xp[b] = L.take(npcg * 6 * 8);
   }
-  o.cg_dec = L.take(4);
+  o.cg_dec = L.take(3 * 4);
   o.part_rr = L.take(npcg * 8);
   o.part_cull = L.take(npt * 8);
   o.iter_cost = rep + RL.ic;
@@ -1392,6 +1392,9 @@ void give_cus(int device, int n) {
 }
 }  // namespace bax
 
+// Solves of a problem that launch their PCG per iteration after one that fell back.
+constexpr int kHoldSolves = 16;
+
 struct ba_problem {
   Symbolic sy;
   DevProblem dp;
@@ -1410,6 +1413,7 @@ struct ba_problem {
   bool use_graph = true;
   bool pcg_steps = false;  // BA_PCG_PER_LAUNCH
   bool one = false;        // the last solve ran its linear solves in one launch each
+  int hold = 0;            // solves yet to launch their PCG per iteration after one that fell back
   // the launch sequence of one solve, captured once: with the PCG as this problem runs it,
   // and launched per iteration, for when that was asked for or the one-launch run's CUs are
   // taken
@@ -2015,7 +2019,11 @@ int ba_solve_async(ba_problem *p) {
   const int per_wg = flagged ? 1 : sy.pcg_run;
   // (one workgroup waits for no other)
   const int n = per_wg && !sy.pcg_small ? ((sy.Cf + sy.pcg_rows - 1) / sy.pcg_rows + per_wg - 1) / per_wg : 0;
-  const bool one = !p->pcg_steps && (sy.pcg_small || (n > 0 && take_cus(p->device, n, flagged)));
+  // (after a solve that fell back the next kHoldSolves launch per iteration: a fall-back
+  // means that other work has the CUs, and costs the wait for them)
+  const bool hold = p->hold > 0 && !flagged && !sy.pcg_small;
+  if (hold) --p->hold;
+  const bool one = !p->pcg_steps && !hold && (sy.pcg_small || (n > 0 && take_cus(p->device, n, flagged)));
   if (one) p->cus = n;
   p->one = one;
   BatchPlan &plan = (p->rig ? p->rig->batch : p->batch).plan;
@@ -2041,6 +2049,7 @@ int ba_wait(ba_problem *p) {
   p->solve_ms = ms;
   std::memcpy(&p->dp.host_state, p->rep_pin + DevProblem::report_state_offset(), sizeof(LMState));
   p->rep_ok = true;
+  if (p->one && p->dp.host_state.pcg_shared) p->hold = kHoldSolves;
   if (p->profiling) p->timer.collect(p->kernel_ms, p->kernel_launches);
   p->solved = true;
   return BA_OK;
@@ -2383,15 +2392,17 @@ int ba_set_pcg_form(ba_problem *p, int32_t form) {
   if (!p) return fail(BA_EINVAL, "problem is NULL");
   if (form != BA_PCG_AUTO && form != BA_PCG_PER_LAUNCH) return fail(BA_EINVAL, "unknown PCG form %d", form);
   p->pcg_steps = form == BA_PCG_PER_LAUNCH;
+  p->hold = 0;
   return BA_OK;
 }
 
-int ba_get_pcg_form(const ba_problem *p, int32_t *form) {
+int ba_get_pcg_form(const ba_problem *p, int32_t *form, int32_t *fell_back) {
   if (!p || !form) return fail(BA_EINVAL, "NULL argument");
   if (p->pending) return fail(BA_ESTATE, "a solve is in flight");
   if (!p->solved) return fail(BA_ESTATE, "no solve has run since the last reset");
   *form = p->one && one_reduction_pcg(p->dp.precision, p->rig ? p->rig->sy.max_tcols : p->dp.max_tcols)
               ? BA_PCG_AUTO : BA_PCG_PER_LAUNCH;
+  if (fell_back) *fell_back = p->dp.host_state.pcg_shared;
   return BA_OK;
 }
 
@@ -2547,7 +2558,7 @@ hipError_t DevProblem::enqueue_result(hipStream_t s, char *pinned) const {
   return e;
 }
 
-void DevProblem::finish_result(const char *pinned, ba_pose *poses_out, double *points_out, ba_report *rep) const {
+int DevProblem::finish_result(const char *pinned, ba_pose *poses_out, double *points_out, ba_report *rep) const {
   const ResultLayout L(C, P, view.n_pt_tiles, max_iters);
   LMState st;
   std::memcpy(&st, pinned + L.st, sizeof(LMState));
@@ -2559,7 +2570,7 @@ void DevProblem::finish_result(const char *pinned, ba_pose *poses_out, double *p
   if (points_out)
     for (int j = 0; j < P; ++j)
       for (int m = 0; m < 3; ++m) points_out[3 * (size_t)pt_order[j] + m] = X[3 * (size_t)j + m];
-  if (!rep) return;
+  if (!rep) return st.pcg_shared;
   double *ic = rep->iter_cost;
   int32_t *pi = rep->pcg_iters;
   std::memset(rep, 0, sizeof(*rep));
@@ -2583,6 +2594,7 @@ void DevProblem::finish_result(const char *pinned, ba_pose *poses_out, double *p
   rep->rms_px = (n_active - masked) > 0 ? std::sqrt(tot / (double)(n_active - masked)) : 0.0;
   if (ic) std::memcpy(ic, pinned + L.ic, ((size_t)st.iter + 1) * 8);
   if (pi && st.iter > 0) std::memcpy(pi, pinned + L.pi, (size_t)st.iter * 4);
+  return st.pcg_shared;
 }
 
 int DevProblem::read_result(hipStream_t s, ba_pose *poses_out, double *points_out, ba_report *rep,

@@ -89,7 +89,8 @@ struct LMState {
   int32_t pcg_fault;       // 1: a wait of the one-launch PCG timed out (the solve stops)
   int32_t halted;          // 1: the solve ended before max_iters (after such a time-out)
   int32_t bar_polls;       // polls after which a wait of the one-launch PCG gives up ...
-  int32_t bar_from, pad;   // ... from this iteration of a linear solve on (kBarPollsDefault before)
+  int32_t bar_from;        // ... from this iteration of a linear solve on (kBarPollsDefault before)
+  int32_t pcg_shared;      // linear solves of this solve whose one-launch PCG fell back (k_cg_run)
 };
 // Default of LMState::bar_polls: about a second of polling.
 constexpr int32_t kBarPollsDefault = 1 << 20;
@@ -257,7 +258,8 @@ struct ProbDev {
   Gp<double> part_pq;             // [n_pcg_tiles]
   Gp<double> part_cg[2];          // [3][n_pcg_tiles] r.u, w.u, r.r partials by parity
   Gp<uint64_t> cg_xw[2];          // [6 Cf][words of T] resident PCG: stamped w by parity (see k_cg_run)
-  Gp<uint32_t> cg_dec;            // resident PCG that may fall back: the decision word
+  Gp<uint32_t> cg_dec;            // resident PCG that may fall back: the decision word, and the
+                                  // steps taken and ended after a fall-back
   Gp<uint64_t> cg_xp[2];          // [6][n_pcg_tiles] ... stamped words of the r.u, w.u, r.r partials
   Gp<double> part_rr;             // [n_pcg_tiles]
   Gp<int32_t> part_cull;          // [n_pt_tiles][2] active observations, points with one, after culling
@@ -285,8 +287,8 @@ struct BatchPlan {
   int32_t big_rows;  // ... by those whose PCG takes more than one workgroup
   int32_t pcg_steps; // 1: a launch per PCG iteration for every problem, also where one workgroup
                      // or the flag's resident run would do (ba_set_pcg_form)
-  int32_t pcg_run;   // the PCG in one launch that falls back to one workgroup when its tiles
-                     // cannot all run at once: tiles per workgroup, 0: a launch per iteration
+  int32_t pcg_run;   // the PCG in one launch that falls back when its tiles cannot all run at
+                     // once: tiles per workgroup, 0: a launch per iteration
   ProbDev single;  // host copy of the descriptor when n_probs == 1 (passed by value to short kernels)
 };
 

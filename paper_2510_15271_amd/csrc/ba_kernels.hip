@@ -1948,7 +1948,7 @@ __global__ __launch_bounds__(64 * NW) void k_cg_start(const ProbDev *__restrict_
     const int ne = 6 * cg_words<T>() * (min(pd.Cf, (tl.idx + 1) * pd.pcg_rows) - tl.idx * pd.pcg_rows);
     for (int k = threadIdx.x; k < ne; k += 64 * NW)
       for (int b = 0; b < 2; ++b) pd.cg_xw[b][e0 + k] = 0u;
-    if (tl.idx == 0 && threadIdx.x == 0) *pd.cg_dec = 0u;
+    if (tl.idx == 0 && threadIdx.x < 3) pd.cg_dec[threadIdx.x] = 0u;
     if (threadIdx.x < 12) pd.cg_xp[threadIdx.x / 6][(size_t)(threadIdx.x % 6) * pd.n_pcg_tiles + tl.idx] = 0u;
   }
   if (threadIdx.x == 0) s_flag[0] = lm_active(st) ? 1 : 0;
@@ -2081,7 +2081,9 @@ __device__ inline void cg_column(int m, T tb, T ta, const T (&w0)[6], const T (&
 }
 
 // RC: the rows per tile when the launch knows them (4, 16, 32), else 0 (read per problem).
-template <class T, int RC>
+// SHARED: not a launch of its own but one of cg_share's steps, where a thread of its own
+// must not leave before the others.
+template <class T, int RC, bool SHARED = false>
 __device__ __forceinline__ void cg_step_body(const ProbDev &pd, const int tile, int it) {
   extern __shared__ double s_dyn[];
   T *ul = (T *)s_dyn;  // [tile columns][6]: u_{it+1} of every column this tile reads
@@ -2096,7 +2098,7 @@ __device__ __forceinline__ void cg_step_body(const ProbDev &pd, const int tile, 
   // graph of an LM iteration holds every allowed PCG step, and once the PCG has
   // converged the rest only pass through here.  (A tile that sees the flag its own
   // launch's tile 0 has just set leaves as it would after its own convergence test.)
-  if (!(lm_active(st) && !st->pcg_done && it < st->pcg_max)) return;
+  if (!SHARED && !(lm_active(st) && !st->pcg_done && it < st->pcg_max)) return;
   const int t = threadIdx.x;
   const int pr = it & 1, cu = (it + 1) & 1;
   const int nt = pd.n_pcg_tiles;
@@ -2437,9 +2439,9 @@ __device__ __forceinline__ T stamped_value(const uint64_t *v) {
 // Unless the caller asked for the run by flag, it falls back (fall_back): where a wait runs
 // out (the first one, for all tiles to have published their first products, after
 // kCgGatherPolls polls), one word, set by the first tile to give up or to finish, sends every
-// tile out before it has changed anything, and tile 0 runs the per-launch steps of all tiles
-// by itself.  Where the word says that a tile has finished, that tile has read every word
-// that is still waited for, so the wait goes on.
+// tile out before it has changed anything, and the workgroups that run share the per-launch
+// steps of all tiles (cg_share).  Where the word says that a tile has finished, that tile has
+// read every word that is still waited for, so the wait goes on.
 constexpr int kCgRunTiles = 320;                                  // tiles at most
 constexpr int kCgRunFew = 16;                                      // up to which polls do not get in each other's way
 constexpr int kCgWaveCols = 10;                                   // columns per wave and set
@@ -2464,9 +2466,9 @@ size_t cg_run_lds_bytes(int max_tcols, size_t tbytes, int per_wg) {
          6 * sizeof(double) * kCgThreads * (per_wg == 2 || max_tcols > kCgSetCols ? 2 : 1);
 }
 
-// The word by which a grid of a falling-back run agrees whether all its tiles take part
-// (kCgGo) or tile 0 alone (kCgSolo): the first decision stands.  Returns the standing one.
-constexpr uint32_t kCgGo = 1, kCgSolo = 2;
+// The word by which a grid of a falling-back run agrees whether all its tiles run to the end
+// (kCgGo) or share the steps (kCgShare): the first decision stands.  Returns the standing one.
+constexpr uint32_t kCgGo = 1, kCgShare = 2;
 __device__ __forceinline__ uint32_t cg_decide(global_t<uint32_t> *dec, uint32_t mine) {
   uint32_t was = 0;
   __hip_atomic_compare_exchange_strong(dec, &was, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -2477,18 +2479,57 @@ __device__ __forceinline__ uint32_t cg_decision(global_t<uint32_t> *dec) {
       (int)__hip_atomic_load(dec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
 // Polls of the first exchange after which a falling-back run takes it that some tile is
-// not running (about 15 ms: longer than kernels that merely have the CUs first).
-constexpr int kCgGatherPolls = 1 << 14;
+// not running (about 15 ms: longer than kernels that merely have the CUs first), and in the
+// linear solves of a solve that has fallen back before.
+constexpr int kCgGatherPolls = 1 << 14, kCgGatherAgain = 1 << 8;
 
-// The PCG of one problem by one workgroup: the per-launch steps of all tiles, one after
-// another (out of line: its registers are not the run's).
+// The PCG of one problem by the workgroups that come here, however many those are and
+// whenever they come: each takes the next (iteration, tile) of the per-launch form, waits
+// until every tile of the iteration before has ended, runs that step and counts it.  A step
+// that is waited for has been taken by a workgroup that runs and waits for earlier steps
+// only, so that any number of workgroups, one alone too, gets to the end.  (Out of line: its
+// registers are not the run's.  One workgroup by itself took 860 ms for a solve of the
+// 500-camera drive that falls back in all of its 10 linear solves, its 125 workgroups take
+// 31; a launch per iteration takes 7.9.)
 template <class T, int R>
-__device__ __noinline__ void cg_solo(const ProbDev *pd, int n_iter) {
-  for (int it = 0; it < n_iter; ++it)
-    for (int k = 0; k < pd->n_pcg_tiles; ++k) {
-      __syncthreads();
-      cg_step_body<T, R>(*pd, k, it);
+__device__ __noinline__ void cg_share(const ProbDev *pd, int n_iter) {
+  __shared__ int s_next;
+  LMState *st = pd->st;
+  const auto dec = as_global(pd->cg_dec);
+  const int nt = pd->n_pcg_tiles;
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      const int n = (int)__hip_atomic_fetch_add(dec + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int need = n / nt * nt;  // the steps of the iterations before
+      if (n == 0) st->pcg_shared += 1;
+      s_next = n / nt < n_iter ? n : -1;
+      for (int left = kBarPollsDefault; s_next >= 0; --left) {
+        if (__hip_atomic_load(&st->pcg_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) {
+          s_next = -1;  // (the tiles of an iteration that converged have nothing to do)
+        } else if ((int)__hip_atomic_load(dec + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= need) {
+          break;
+        } else if (left == 0) {  // (a running workgroup has stood still for about a second)
+          st->pcg_fault = 1;
+          __hip_atomic_store(&st->pcg_done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        __builtin_amdgcn_s_sleep(4);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");  // what was written before the counts
     }
+    __syncthreads();
+    const int n = s_next;
+    if (n < 0) return;
+    cg_step_body<T, R, true>(*pd, n % nt, n / nt);
+    // every wave's stores have arrived, one wave writes them back (each by itself took 140 us
+    // per iteration of 125 tiles)
+    __asm__ volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(dec + 2, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
 }
 
 // Workgroup wg runs tiles TP wg .. TP wg + TP - 1; with TP = 2 the second column set holds
@@ -2530,6 +2571,7 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
   n_iter = min(n_iter, st->pcg_max);
   const double tol = st->pcg_tol, bb = st->pcg_bb;
   const int polls = st->bar_polls, polls_from = st->bar_from;
+  const int gather = st->pcg_shared ? kCgGatherAgain : kCgGatherPolls;
   const auto dec = as_global(pd.cg_dec);
   // ---- per-solve constants and the state of the tile's columns and own rows
   const bool col_lane = lane < 6 * kCgWaveCols;
@@ -2616,18 +2658,18 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
       uint64_t xv[NS][W], pv[2];
       bool lost = false, go = false;
       int lim = it < polls_from ? kBarPollsDefault : polls;
-      if (fall_back && it == 1) lim = min(lim, kCgGatherPolls);
+      if (fall_back && it == 1) lim = min(lim, gather);
       for (int n = 0; !all && !lost; ++n) {
         if (n >= lim) {
           if (!fall_back || go) break;
           // one word decides for the whole grid
-          lost = cg_decide(dec, kCgSolo) == kCgSolo;
+          lost = cg_decide(dec, kCgShare) == kCgShare;
           if (lost) break;
           go = true;  // some tile has finished: the words are on their way
           n = 0;
           lim = kBarPollsDefault;
-        } else if (fall_back && (n & 255) == 255) {
-          lost = cg_decision(dec) == kCgSolo;
+        } else if (fall_back && (n & 63) == 63) {
+          lost = cg_decision(dec) == kCgShare;
         }
 #pragma unroll
         for (int k = 0; k < NS; ++k)
@@ -2802,13 +2844,13 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
     }
   }
   if (fall_back) {
-    // a tile that gave up has every tile leave the solve as k_cg_start left it, and tile 0
-    // run the per-launch steps of all tiles one after another
+    // a tile that gave up has every tile leave the solve as k_cg_start left it, and share
+    // the per-launch steps of all tiles (by the test hook's bound of 0: one workgroup)
     __syncthreads();
     if (t == 0) s_flag[1] = ok ? (int)cg_decide(dec, kCgGo) : 0;
     __syncthreads();
-    if (s_flag[1] == (int)kCgSolo) {
-      if (wg == 0) cg_solo<T, R>(dpd, n_iter);
+    if (s_flag[1] == (int)kCgShare) {
+      if (wg == 0 || polls > 0 || polls_from > 1) cg_share<T, R>(dpd, n_iter);
       return;
     }
   } else if (polls <= 0 && polls_from <= 1) {
@@ -2884,7 +2926,7 @@ __device__ __forceinline__ void cg_small_body(const ProbDev &pd, const ProbDev *
   n_iter = min(n_iter, st->pcg_max);
   if (st->bar_polls <= 0 && st->bar_from <= 1) {  // the test hook: as a run whose workgroups do not meet
     if (fall_back) {
-      cg_solo<T, kPcgRows>(dpd, n_iter);
+      cg_share<T, kPcgRows>(dpd, n_iter);
     } else if (t == 0) {
       st->pcg_fault = 1;
       st->pcg_done = 1;
@@ -4740,7 +4782,7 @@ static hipError_t launch_pcg(const BatchPlan &bp, int pcg_max, int max_tcols, hi
   if (bp.n_pcs && !bp.pcg_steps) {  // the problems that one workgroup solves
     void *args1[] = {(void *)&bp.single, (void *)&bp.probs, (void *)&pcg_max, (void *)&fall_back};
     void *argsn[] = {(void *)&bp.probs, (void *)&bp.pcs, (void *)&pcg_max};
-    const unsigned lds = 6 * cg_small_cams<T>() * sizeof(T);  // for cg_solo
+    const unsigned lds = 6 * cg_small_cams<T>() * sizeof(T);  // for cg_share
     const hipError_t le =
         lone ? hipLaunchKernel((const void *)k_cg_small<T>, dim3(1), dim3(kCgThreads), args1, lds, s)
              : hipLaunchKernel((const void *)k_cg_small_batch<T>, dim3(bp.n_pcs), dim3(kCgThreads), argsn, lds, s);

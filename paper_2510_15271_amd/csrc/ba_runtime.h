@@ -137,10 +137,10 @@ struct DevProblem {
   // of everything the report needs (the state, both pose and point buffers, the
   // evaluation partials and the per-iteration arrays) into `pinned`, a page-locked
   // buffer of result_bytes(); once they have landed, finish_result builds the outputs
-  // from it alone.
+  // from it alone.  Returns how many linear solves fell back from their one launch.
   size_t result_bytes() const;
   hipError_t enqueue_result(hipStream_t s, char *pinned) const;
-  void finish_result(const char *pinned, ba_pose *poses_out, double *points_out, ba_report *rep) const;
+  int finish_result(const char *pinned, ba_pose *poses_out, double *points_out, ba_report *rep) const;
 };
 
 // Tile lists of a set of problems, mirrored on the device.

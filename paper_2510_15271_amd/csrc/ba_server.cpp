@@ -153,6 +153,7 @@ struct Completion {
   hipEvent_t ev = nullptr;
 };
 
+constexpr int kHoldSteps = 256;  // LM steps launched per PCG iteration after a fall-back
 constexpr int kLookahead = 2;  // launch sequences the scheduler may run ahead of the device
 // Later problems that may be admitted ahead of one that waits for memory; past that,
 // admission waits for it, so that a large request is not starved by small ones.
@@ -199,6 +200,7 @@ struct ba_server {
   Batch batch, fin_batch;
   int device = 0;
   int cus = 0;  // CUs taken for one-launch PCG runs, while there is work in flight
+  int64_t hold_until = 0;  // step from which one-launch runs are tried again after a fall-back
   hipEvent_t ev_step[kLookahead] = {};
   int64_t n_steps = 0;
   std::vector<Pinned> pinned_free;
@@ -351,7 +353,10 @@ int ba_server::complete(bool block) {
       r.iter_pcg.resize(r.dp.max_iters);
       r.rep.iter_cost = r.iter_cost.data();
       r.rep.pcg_iters = r.iter_pcg.data();
-      r.dp.finish_result(c.bufs[i].p, r.out_poses.data(), r.out_pts.data(), &r.rep);
+      if (r.dp.finish_result(c.bufs[i].p, r.out_poses.data(), r.out_pts.data(), &r.rep)) {
+        hold_until = n_steps + kHoldSteps;  // other work has the CUs
+        batch.plan.pcg_run = 0;
+      }
       pinned_free.push_back(c.bufs[i]);
     }
     (void)hipEventDestroy(c.ev);
@@ -367,7 +372,7 @@ int ba_server::complete(bool block) {
 // CUs stay taken until the server is idle (earlier launches may still be running).
 int ba_server::batch_run(int max_tcols) {
   const int rows = batch.plan.big_rows, n = batch.plan.n_pcb;
-  if (n == 0 || rows == 0 || n > device_cus()) return 0;
+  if (n == 0 || rows == 0 || n > device_cus() || n_steps < hold_until) return 0;
   // A lone request of fewer than 16 tiles (64 cameras) keeps a launch per iteration: the
   // serving test that has a request overtake a waiting one keeps a lone 60-camera request
   // of 300 iterations in flight for over 50 ms, and in one launch each (41 ms against 86)

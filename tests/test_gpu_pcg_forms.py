@@ -94,7 +94,10 @@ def test_a_wait_that_runs_out_falls_back_at_any_iteration(balib, prec, case):
     last = KW["pcg_max_iters"] - 1
     for it in (1, 2, 7, last):
         _say("device solves:", case, prec, "waits give up from iteration", it)
-        _same(ref, p.set_barrier_polls(0, it).reset().solve().result())
+        p.set_barrier_polls(0, it).set_pcg_form(balib.PCG_AUTO)
+        _same(ref, p.reset().solve().result())
+        assert p.pcg_form() == balib.PCG_AUTO
+        assert p.pcg_fell_back() == sum(n >= it for n in ref["pcg_iters"])
     p.close()
     if case in ("rig", "graph pairs"):
         return
@@ -105,6 +108,30 @@ def test_a_wait_that_runs_out_falls_back_at_any_iteration(balib, prec, case):
             assert r["status"] == balib.STATUS_PCG_SYNC and r["iters"] == 1 and r["accepted"] == 0
         else:
             assert max(ref["pcg_iters"]) >= it or r["status"] == ref["status"]
+    p.close()
+
+
+@pytest.mark.parametrize("first", [1, 2])
+def test_a_fall_back_is_remembered(balib, first):
+    """After a solve that fell back (one workgroup runs the steps, or all share them) the
+    next 16 launch their PCG per iteration, then one launch is tried again; asking for the
+    default form tries it at once.  A flagged solve and one that did not fall back hold
+    nothing back."""
+    p = _problem(balib, "41 cameras", "f32").set_barrier_polls(0, first)
+    ref = p.solve().result()
+    assert p.pcg_form() == balib.PCG_AUTO and p.pcg_fell_back() == 3
+    p.set_barrier_polls(1 << 20)
+    for _ in range(16):
+        _same(ref, p.reset().solve().result())
+        assert p.pcg_form() == balib.PCG_PER_LAUNCH and p.pcg_fell_back() == 0
+    for _ in range(2):
+        _same(ref, p.reset().solve().result())
+        assert p.pcg_form() == balib.PCG_AUTO and p.pcg_fell_back() == 0
+    p.set_barrier_polls(0, first).reset().solve()
+    assert p.pcg_fell_back() == 3
+    p.set_barrier_polls(1 << 20).set_pcg_form(balib.PCG_AUTO)
+    _same(ref, p.reset().solve().result())
+    assert p.pcg_form() == balib.PCG_AUTO and p.pcg_fell_back() == 0
     p.close()
 
 
