@@ -372,6 +372,15 @@ int ba_server::complete(bool block) {
 // CUs stay taken until the server is idle (earlier launches may still be running).
 int ba_server::batch_run(int max_tcols) {
   const int rows = batch.plan.big_rows, n = batch.plan.n_pcb;
+  // a lone request with BA_FLAG_PCG_RESIDENT runs in one launch in any case: counted, as a
+  // flagged solve is
+  if (n > 0 && batch.probs.size() == 1 && batch.probs[0].pcg_resident) {
+    if (n > cus) {
+      (void)take_cus(device, n - cus, true);
+      cus = n;
+    }
+    return 1;
+  }
   if (n == 0 || rows == 0 || n > device_cus() || n_steps < hold_until) return 0;
   // A lone request of fewer than 16 tiles (64 cameras) keeps a launch per iteration: the
   // serving test that has a request overtake a waiting one keeps a lone 60-camera request

@@ -1,6 +1,8 @@
 """The forms of the block-Jacobi PCG (one launch per linear solve by several workgroups or
 by one, asked for by flag or chosen by size, alone or in a served batch) against one launch
 per PCG iteration, which ba_set_pcg_form selects.  Needs an MI355X."""
+import time
+
 import numpy as np
 import pytest
 
@@ -187,6 +189,33 @@ def test_served_batches_of_both_forms(balib, prec):
         for t, ref in zip(ts, refs):
             _same(ref, srv.wait(t))
         srv.close()
+
+
+def test_a_flagged_request_counts_its_cus(balib):
+    """A lone server request with the resident flag (14 tiles) runs in one launch in any case,
+    so its CUs count: a solve of 250 tiles beside it, which they no longer hold, launches per
+    iteration, and one after it does not."""
+    A = make_small_drive(57, 6000, seed=140)
+    s = make_small_drive(1000, 9000, seed=3)
+    kw = dict(max_iters=3, pcg_max_iters=20, precision="f32")
+    p = balib.Problem.from_scene(s, **kw)
+    ref = p.solve().result()
+    assert p.pcg_form() == balib.PCG_AUTO and p.info()["pcg_rows"] == 4
+    srv = balib.Server(1 << 28, 2, "f32")
+    t = srv.submit(balib.scene_desc(A), balib.options(max_iters=4000, precision="f32", flags=RESIDENT))
+    time.sleep(0.1)  # the request is running
+    t0 = time.perf_counter()
+    b = p.reset().solve().result()
+    form, ended = p.pcg_form(), time.perf_counter()
+    r = srv.wait(t)
+    _say("request latency", r["latency_ms"], "ms, solve beside it ended after", 100 + 1e3 * (ended - t0), "ms, form", form)
+    assert r["latency_ms"] > 100 + 1e3 * (ended - t0)  # it was still running
+    assert form == balib.PCG_PER_LAUNCH
+    _same(ref, b)
+    srv.close()
+    _same(ref, p.reset().solve().result())
+    assert p.pcg_form() == balib.PCG_AUTO
+    p.close()
 
 
 def test_profiled_per_launch_runs(balib):
