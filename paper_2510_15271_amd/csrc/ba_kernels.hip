@@ -3059,6 +3059,10 @@ __device__ __forceinline__ void cg_small_body(const ProbDev &pd, const ProbDev *
           for (int j = 0; j < 3; ++j) s_pd[j][k] = v[j];
         }
       }
+      // the wave's other lanes read the partials next
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
       totals();
     }
   }
