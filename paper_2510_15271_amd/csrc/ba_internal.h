@@ -82,15 +82,15 @@ struct LMState {
   double lambda0, pcg_tol, huber_delta;
   double pcg_bb, pcg_rz0;  // ||b||^2 and r0.z0 of the current linear solve
   double cg_alpha[2], cg_gamma[2];  // alpha_i, gamma_i of the one-reduction form, by parity
-  double sq_sum;           // sum ||r||^2 at the final state (evaluation kernel)
+  int32_t bar_from;        // see bar_polls
+  int32_t pcg_shared;      // linear solves of this solve whose one-launch PCG fell back (k_cg_run)
   int32_t iter, max_iters, relin, status;
   int32_t accepted, cur, pcg_done, pcg_iters;
   int32_t pcg_max, init_done, n_masked;
   int32_t pcg_fault;       // 1: a wait of the one-launch PCG timed out (the solve stops)
   int32_t halted;          // 1: the solve ended before max_iters (after such a time-out)
-  int32_t bar_polls;       // polls after which a wait of the one-launch PCG gives up ...
-  int32_t bar_from;        // ... from this iteration of a linear solve on (kBarPollsDefault before)
-  int32_t pcg_shared;      // linear solves of this solve whose one-launch PCG fell back (k_cg_run)
+  int32_t bar_polls;       // polls after which a wait of the one-launch PCG gives up, from
+                           // iteration bar_from of a linear solve on (kBarPollsDefault before)
 };
 // Default of LMState::bar_polls: about a second of polling.
 constexpr int32_t kBarPollsDefault = 1 << 20;

@@ -2433,9 +2433,9 @@ __device__ __forceinline__ T stamped_value(const uint64_t *v) {
 // with more than 160 columns takes a second set of ten per wave (NS = 2).
 // Against the grid-barrier form, which exchanged w, s and r, read by all six lanes of a
 // column, an iteration of the 500-camera drive (2.3M observations) went from 8.4 to
-// 3.7 us; against a launch per iteration, the 203-camera submap went from 8.5 to 3.7 us, a
-// 24-camera window from 6.1 to 3.3, the 9000-node pose graph from 13.8 to 5.6 and the
-// 3000-camera loop from 25 (with the launches that find the solve converged) to 15.
+// 3.7 us; against a launch per iteration, the 203-camera submap went from 8.5 to 3.6 us, the
+// 9000-node pose graph from 13.8 to 5.5 and the 3000-camera loop from 25 (with the launches
+// that find the solve converged) to 15.
 // Unless the caller asked for the run by flag, it falls back (fall_back): where a wait runs
 // out (the first one, for all tiles to have published their first products, after
 // kCgGatherPolls polls), one word, set by the first tile to give up or to finish, sends every
@@ -2443,7 +2443,7 @@ __device__ __forceinline__ T stamped_value(const uint64_t *v) {
 // steps of all tiles (cg_share).  Where the word says that a tile has finished, that tile has
 // read every word that is still waited for, so the wait goes on.
 constexpr int kCgRunTiles = 320;                                  // tiles at most
-constexpr int kCgRunFew = 16;                                      // up to which polls do not get in each other's way
+constexpr int kCgRunFew = 16;                                      // tiles up to which a short pause is enough
 constexpr int kCgWaveCols = 10;                                   // columns per wave and set
 constexpr int kCgSetCols = kCgWaveCols * (kCgThreads / 64);      // 160
 // S blocks per lane group held for the whole solve: what fits 128 VGPRs (16 waves per CU)
@@ -2649,10 +2649,13 @@ __device__ __forceinline__ void cg_run_body(const ProbDev &pd, const ProbDev *dp
       const auto xw = (it & 1) ? xw1 : xw0, xp = (it & 1) ? xp1 : xp0;
       const uint32_t stamp = (uint32_t)it;
       // the first poll waits about as long as the values take: polls that come too early
-      // queue up in front of the stores they wait for (125 tiles: 6.3 us per iteration
-      // without the pause, 4.5 at 15 units of 64 clocks, 3.7 at 25, 4.0 at 40; 2 tiles: 5.1,
-      // 4.4 at 10, 4.6 at 25)
-      if (nt > kCgRunFew) __builtin_amdgcn_s_sleep(25);
+      // queue up in front of the stores they wait for, the more the more tiles there are.  us
+      // per iteration in FP32 at a pause of 1, 10, 20, 22, 25 and 35 units of 64 clocks: 11
+      // tiles 3.78, 3.39, 3.45, -, 3.60, 3.85; 16 tiles 4.57, 3.50, 3.49, -, 3.61, 3.86; 25
+      // tiles 4.55, 3.80, 3.49, 3.51, 3.58, 3.83; 51 tiles 5.19, 4.09, 3.57, 3.56, 3.61, 3.86;
+      // 125 tiles 5.98, 4.59, 3.73, 3.71, 3.75, 4.01; 141 pairs of 32-row tiles 6.79, 5.85,
+      // 5.48, 5.50, 5.55, 5.81; 188 tiles of 16 rows 13.6, 13.5, 13.04, 12.98, 12.91, 12.7
+      if (nt > kCgRunFew) __builtin_amdgcn_s_sleep(22);
       else __builtin_amdgcn_s_sleep(10);
       bool all = false;
       uint64_t xv[NS][W], pv[2];
@@ -2924,7 +2927,8 @@ __device__ __forceinline__ void cg_small_body(const ProbDev &pd, const ProbDev *
   __syncthreads();
   if (!s_flag[0]) return;
   n_iter = min(n_iter, st->pcg_max);
-  if (st->bar_polls <= 0 && st->bar_from <= 1) {  // the test hook: as a run whose workgroups do not meet
+  const int polls = st->bar_polls, polls_from = st->bar_from;
+  if ((polls <= 0) & (polls_from <= 1)) {  // the test hook: as a run whose workgroups do not meet
     if (fall_back) {
       cg_share<T, kPcgRows>(dpd, n_iter);
     } else if (t == 0) {
