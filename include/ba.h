@@ -124,7 +124,10 @@ typedef struct {
    cooperative launch, so the runtime itself places every workgroup at once (or fails the
    launch) instead of relying on the occupancy count alone; for callers that share the
    device with other work.  Costs about 20 us per linear solve on an idle device.  No
-   effect without BA_FLAG_PCG_RESIDENT or where the resident form does not fit. */
+   effect without BA_FLAG_PCG_RESIDENT or where the resident form does not fit, and none
+   on a linear solve that one workgroup runs (up to 40 free cameras, 24 in BA_PREC_F64):
+   that is an ordinary launch, since one workgroup waits for no other, although
+   ba_problem_info.pcg_resident reports 2 there too. */
 #define BA_FLAG_PCG_COOPERATIVE 64
 /* BA_FLAG_DENSE_SCHUR: form the Schur complement in its dense co-visibility form, used
    by default when at most 1024 cameras are free, a point is seen by at least a quarter
@@ -288,7 +291,7 @@ typedef struct {
                              1024 free cameras 16, or 32 beyond 8192 free cameras
                              (4 again where a tile's columns would not fit in LDS)     */
   int32_t pcg_resident;   /* 1: BA_FLAG_PCG_RESIDENT was asked for and the problem fits it;
-                             2: the same, started as a cooperative launch                  */
+                             2: the same with BA_FLAG_PCG_COOPERATIVE                      */
 } ba_problem_info;
 int ba_get_info(const ba_problem *p, ba_problem_info *out);
 /* The symbolic analysis of ba_create alone, for planning: validates d and opt as
