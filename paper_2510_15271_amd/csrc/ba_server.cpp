@@ -199,7 +199,8 @@ struct ba_server {
   std::vector<std::thread> ana_th;
   Batch batch, fin_batch;
   int device = 0;
-  int cus = 0;  // CUs taken for one-launch PCG runs, while there is work in flight
+  int cus = 0;  // CUs taken for the one-launch PCG runs of the steps in flight
+  int step_cus[kLookahead] = {};  // CUs of the last steps' runs
   int64_t hold_until = 0;  // step from which one-launch runs are tried again after a fall-back
   hipEvent_t ev_step[kLookahead] = {};
   int64_t n_steps = 0;
@@ -217,6 +218,7 @@ struct ba_server {
   Pinned take_pinned(size_t n);
   int complete(bool block);
   int batch_run(int max_tcols);
+  void trim_cus();
   bool idle_locked() const {
     return ana_q.empty() && analysing == 0 && ready.empty() && pose_q.empty() && up_q.empty() &&
            uploading == 0 && uploaded.empty() && active.empty() && completing.empty();
@@ -368,8 +370,8 @@ int ba_server::complete(bool block) {
 }
 
 // Whether the batch's linear solves run in one launch: every problem's tiles at once, one
-// workgroup each, where the device holds them beside the other such runs in flight.  The
-// CUs stay taken until the server is idle (earlier launches may still be running).
+// workgroup each, where the device holds them beside the other such runs in flight.  Takes
+// the CUs beyond those taken already (trim_cus gives back).
 int ba_server::batch_run(int max_tcols) {
   const int rows = batch.plan.big_rows, n = batch.plan.n_pcb;
   // a lone request with BA_FLAG_PCG_RESIDENT runs in one launch in any case: counted, as a
@@ -394,6 +396,13 @@ int ba_server::batch_run(int max_tcols) {
     cus = n;
   }
   return 1;
+}
+
+// Gives back the CUs beyond what the last steps may still use.
+void ba_server::trim_cus() {
+  const int n = *std::max_element(step_cus, step_cus + kLookahead);
+  if (cus > n) give_cus(device, cus - n);
+  cus = std::min(cus, n);
 }
 
 void ba_server::loop() {
@@ -467,6 +476,9 @@ void ba_server::loop() {
       // at most kLookahead launch sequences in flight
       hipEvent_t &ev = ev_step[n_steps % kLookahead];
       if (fatal == BA_OK && n_steps >= kLookahead && hipEventSynchronize(ev) != hipSuccess) fatal = BA_EDEVICE;
+      // the step that used this slot has ended, and with it the use of its CUs
+      step_cus[n_steps % kLookahead] = batch.plan.pcg_run ? batch.plan.n_pcb : 0;
+      if (fatal == BA_OK) trim_cus();
       if (fatal == BA_OK &&
           launch_lm_iteration(precision, batch.plan, pcg_max, max_cf, stream, nullptr) != hipSuccess)
         fatal = BA_EDEVICE;
@@ -536,15 +548,15 @@ void ba_server::loop() {
       const bool nothing_launched = pose_now.empty() && active.empty();
       if (complete(nothing_launched) != BA_OK) fatal = BA_EDEVICE;
       if (cus && active.empty() && completing.empty()) {  // every launch's results have landed
-        give_cus(device, cus);
-        cus = 0;
+        std::fill(step_cus, step_cus + kLookahead, 0);
+        trim_cus();
       }
     }
     if (fatal != BA_OK) {
       // fail everything still pending; the device state is unknown
       (void)hipStreamSynchronize(stream);
-      if (cus) give_cus(device, cus);
-      cus = 0;
+      std::fill(step_cus, step_cus + kLookahead, 0);
+      trim_cus();
       std::vector<ReqP> all;
       {
         std::lock_guard<std::mutex> lk(mu);

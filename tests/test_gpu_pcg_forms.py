@@ -218,6 +218,31 @@ def test_a_flagged_request_counts_its_cus(balib):
     p.close()
 
 
+def test_a_server_gives_back_the_cus_of_a_batch_that_shrank(balib):
+    """A long request (18 tiles) beside one of 175 tiles that ends soon: once that has ended, a
+    solve of 230 tiles finds CUs enough, with the long request still running."""
+    A, B = make_small_drive(70, 6000, seed=141), make_small_drive(700, 9000, seed=142)
+    kw = dict(max_iters=3, pcg_max_iters=20, precision="f32")
+    p = balib.Problem.from_scene(make_small_drive(920, 9000, seed=3), **kw)
+    ref = p.solve().result()
+    assert p.pcg_form() == balib.PCG_AUTO and p.info()["pcg_rows"] == 4
+    srv = balib.Server(1 << 28, 4, "f32")
+    tb = srv.submit(balib.scene_desc(B), balib.options(**kw))
+    ta = srv.submit(balib.scene_desc(A), balib.options(max_iters=6000, precision="f32"))
+    t0 = time.perf_counter()
+    srv.wait(tb)
+    time.sleep(0.05)
+    b = p.reset().solve().result()
+    form, ended = p.pcg_form(), time.perf_counter()
+    ra = srv.wait(ta)
+    _say("long request", ra["latency_ms"], "ms, solve beside it ended after", 1e3 * (ended - t0), "ms, form", form)
+    assert ra["latency_ms"] > 1e3 * (ended - t0)  # it was still running
+    assert form == balib.PCG_AUTO and p.pcg_fell_back() == 0
+    _same(ref, b)
+    srv.close()
+    p.close()
+
+
 def test_profiled_per_launch_runs(balib):
     """The PCG timed alone (segment graphs) and launch by launch, switching forms on one
     problem: the same solves, and a run counts its steps unless the flag made it one launch."""
