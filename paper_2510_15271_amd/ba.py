@@ -561,25 +561,39 @@ _POSE_RECORD = np.dtype(dict(names=["K", "pose0", "n", "X", "uv"],
                              itemsize=C.sizeof(PoseRequest)))
 
 
+def _pose_columns(requests, keep):
+    """_pose_requests where every K, q0 and t0 is an array, list or tuple of its usual length
+    with finite values (NumPy makes NaN of a None, which float() refuses); else None."""
+    n = len(requests)
+    cols, X, uv = [], [], []
+    try:
+        for f, w in (("K", 4), ("q0", 4), ("t0", 3)):
+            rows = [getattr(q, f) for q in requests]
+            if not {type(r) for r in rows} <= {np.ndarray, list, tuple}:
+                return None
+            cols.append(np.array(rows, np.float64))
+            if cols[-1].shape != (n, w) or not np.isfinite(cols[-1]).all():
+                return None
+        X = [np.ascontiguousarray(q.X, np.float64) for q in requests]
+        uv = [np.ascontiguousarray(q.uv, np.float64) for q in requests]
+        arr = np.zeros(n, _POSE_RECORD)
+        arr["K"], arr["pose0"][:, :4], arr["pose0"][:, 4:] = cols
+        arr["n"] = [x.shape[0] for x in X]
+    except Exception:  # whatever it is, the records say it request by request
+        return None
+    arr["X"] = [x.__array_interface__["data"][0] for x in X]
+    arr["uv"] = [x.__array_interface__["data"][0] for x in uv]
+    keep += [X, uv, arr]
+    return arr.ctypes.data_as(C.POINTER(PoseRequest))
+
+
 def _pose_requests(requests, keep):
     """The ba_pose_request array of a call, as a pointer (keep holds what it points to).
-    Filled as columns where every K, q0 and t0 has its usual length: one ctypes record after
-    the other took 12 us per request."""
-    if len(requests) >= 16:
-        try:
-            cols = [np.array([getattr(q, f) for q in requests], np.float64) for f in ("K", "q0", "t0")]
-        except ValueError:  # rows of different lengths
-            cols = []
-        if [c.shape for c in cols] == [(len(requests), w) for w in (4, 4, 3)]:
-            X = [np.ascontiguousarray(q.X, np.float64) for q in requests]
-            uv = [np.ascontiguousarray(q.uv, np.float64) for q in requests]
-            arr = np.zeros(len(requests), _POSE_RECORD)
-            arr["K"], arr["pose0"][:, :4], arr["pose0"][:, 4:] = cols
-            arr["n"] = [x.shape[0] for x in X]
-            arr["X"] = [x.__array_interface__["data"][0] for x in X]
-            arr["uv"] = [x.__array_interface__["data"][0] for x in uv]
-            keep += [X, uv, arr]
-            return arr.ctypes.data_as(C.POINTER(PoseRequest))
+    Filled by column where that gives what one ctypes record after the other does (12 us per
+    request), which takes the rest and raises the errors."""
+    arr = _pose_columns(requests, keep) if len(requests) >= 16 else None
+    if arr is not None:
+        return arr
     arr = (PoseRequest * len(requests))()
     for i, q in enumerate(requests):
         arr[i] = _pose_request(q.K, q.q0, q.t0, q.X, q.uv, keep)
