@@ -569,7 +569,7 @@ def _pose_columns(requests, keep):
     try:
         for f, w in (("K", 4), ("q0", 4), ("t0", 3)):
             rows = [getattr(q, f) for q in requests]
-            if not {type(r) for r in rows} <= {np.ndarray, list, tuple}:
+            if not set(map(type, rows)) <= {np.ndarray, list, tuple}:
                 return None
             cols.append(np.array(rows, np.float64))
             if cols[-1].shape != (n, w) or not np.isfinite(cols[-1]).all():
@@ -578,7 +578,7 @@ def _pose_columns(requests, keep):
         uv = [np.ascontiguousarray(q.uv, np.float64) for q in requests]
         arr = np.zeros(n, _POSE_RECORD)
         arr["K"], arr["pose0"][:, :4], arr["pose0"][:, 4:] = cols
-        arr["n"] = [x.shape[0] for x in X]
+        arr["n"] = list(map(len, X))
     except Exception:  # whatever it is, the records say it request by request
         return None
     arr["X"] = [x.__array_interface__["data"][0] for x in X]
