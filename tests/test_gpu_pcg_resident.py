@@ -1,6 +1,8 @@
 """The resident PCG (BA_FLAG_PCG_RESIDENT: every iteration of a linear solve in one
-launch, workgroups meeting at a grid barrier) against the launch-per-iteration PCG
-and the FP64 oracle, through the C-ABI.  Needs an MI355X."""
+launch, workgroups handing each other stamped words) against the solve without the flag
+(one launch too, with a fall-back, wherever it fits), its fall-back and the FP64 oracle,
+through the C-ABI.  test_gpu_pcg_forms.py compares both with a launch per PCG iteration.
+Needs an MI355X."""
 import sys
 
 import numpy as np
