@@ -63,7 +63,8 @@ extern "C" {
 #define BA_STATUS_PCG_SYNC 3   /* a wait of the resident PCG timed out (its workgroups
                                   were not all resident at once): the solve stopped with the
                                   step rejected; solve without BA_FLAG_PCG_RESIDENT, where
-                                  such a wait falls back instead                            */
+                                  such a wait falls back instead (and this status means that
+                                  a workgroup that runs stood still for about a second)     */
 
 typedef struct { double fx, fy, cx, cy; } ba_intrinsics;         /* pinhole, no distortion  */
 typedef struct { double qw, qx, qy, qz, tx, ty, tz; } ba_pose;   /* world -> camera         */
